@@ -120,30 +120,76 @@ __device__ __forceinline__ v4i zero4() { return v4i{0, 0, 0, 0}; }
 
 // ------------------------------------------------- fallback (unaligned) loads
 
-// 16 bytes at p[0..15]; bytes with index >= valid read as zero.
-__device__ __forceinline__ v4i load_bytes(const int8_t *p, int valid)
+// Rows of an int8 matrix at any byte alignment.  A 16-byte chunk at byte o of
+// the rows' window is taken as the five aligned dwords from o & ~3 on and
+// funnel-shifted into place (four v_alignbyte_b32) on its way to LDS.  The
+// window starts at the dword holding the first byte and ends with the dword
+// holding the last one, so every dword it reads holds a byte of the matrix;
+// the others are dropped by the buffer bounds.  It is set per output tile,
+// so the matrix itself may exceed the 2 GiB of a buffer offset.
+//
+// Bound by instruction issue and latency like the aligned path: the extra
+// dword load and shifts hide behind the matrix work of the other waves.
+// A call in a row of calls, against byte-by-byte loads (sixteen per chunk):
+// 777x1153 -> 1111 12.6 us (62.5 before, both with 64x64 tiles), 8192x1151 ->
+// 3456 64.2 us (361.7), a 20x30 conv 1275 -> 1280 64.9 us (1217).
+struct Window {
+    rsrc_t r;
+    uint32_t lead;              // bytes before the first row in its dword
+
+    __device__ __forceinline__ void init(const int8_t *base, int rows, int first, int count,
+                                         int K)
+    {
+        const int8_t *p = base + (size_t)first * (size_t)K;
+        lead = (uint32_t)(reinterpret_cast<uintptr_t>(p) & 3u);
+        const int n = min(rows - first, count);
+        const uint32_t bytes = n > 0 ? lead + (uint32_t)n * (uint32_t)K : 0u;
+        r = make_rsrc(p - lead, (bytes + 3u) & ~3u);
+    }
+};
+
+struct Chunk5 {
+    v4i lo;
+    uint32_t hi;
+
+    __device__ __forceinline__ void load(rsrc_t r, uint32_t off)
+    {
+        lo = ld16(r, off & ~3u);
+        hi = __builtin_amdgcn_raw_buffer_load_b32(r, (off & ~3u) + 16u, 0, 0);
+    }
+
+    // The 16 bytes from byte off % 4 of the five dwords on.
+    __device__ __forceinline__ v4i bytes(uint32_t off) const
+    {
+        const uint32_t a = (uint32_t)lo.x, b = (uint32_t)lo.y, c = (uint32_t)lo.z,
+                       d = (uint32_t)lo.w;
+        return v4i{(int)__builtin_amdgcn_alignbyte(b, a, off),
+                   (int)__builtin_amdgcn_alignbyte(c, b, off),
+                   (int)__builtin_amdgcn_alignbyte(d, c, off),
+                   (int)__builtin_amdgcn_alignbyte(hi, d, off)};
+    }
+};
+
+// Keeps the first `valid` bytes of a chunk.
+__device__ __forceinline__ v4i keep_bytes(v4i v, int valid)
 {
-    uint32_t w[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-        if (i < valid)
-            w[i >> 2] |= (uint32_t)(uint8_t)p[i] << (8 * (i & 3));
-    return v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+    auto mask = [&](int w) {
+        const int n = valid - 4 * w;
+        return n >= 4 ? -1 : n <= 0 ? 0 : (1 << (8 * n)) - 1;
+    };
+    v.x &= mask(0);
+    v.y &= mask(1);
+    v.z &= mask(2);
+    v.w &= mask(3);
+    return v;
 }
 
-// Chunk (row, kbyte..kbyte+15) of a row-major [rows][K] int8 matrix, any K.
-__device__ __forceinline__ v4i load_rowmajor_any(const int8_t *base, int rows, int K, int row,
-                                                 int kbyte)
-{
-    if (row >= rows || kbyte >= K)
-        return zero4();
-    return load_bytes(base + (size_t)row * (size_t)K + kbyte, K - kbyte);
-}
-
-// Chunk of the implicit-GEMM activation of a 3x3 / pad 1 conv for any C:
+// Chunk of the implicit-GEMM activation of a 3x3 / pad 1 conv for any C,
+// byte by byte.  Only for what no window chunk serves: packed weights, whose
+// K order lets a chunk cross taps, and a tile whose pixels span 2 GiB.
 // element k of row m = h*Wd + w is X[h + r - 1][w + s - 1][ci] with
 // k = (r*3 + s)*C + ci, or 0 in the padding.
-__device__ __forceinline__ v4i load_conv_any(const LayerDesc &d, int m, int kbyte)
+__device__ __forceinline__ v4i load_conv_bytes(const LayerDesc &d, int m, int kbyte)
 {
     if (m >= d.M || kbyte >= d.K)
         return zero4();
@@ -230,14 +276,19 @@ __device__ __forceinline__ v4i load_planes(const uint32_t *P, int N, int K, int 
 // offset is fixed per tile and advanced by the K step; rows past M (N)
 // carry kOOB and read zero.  Weight chunks at or past the end of the K range
 // read zero as well, so the MFMAs of a ragged last K tile need no masking
-// (the activation bytes there meet zero weights).
+// (the activation bytes there meet zero weights).  Otherwise a chunk's
+// offset is into its operand's byte window (Window); the K bytes a row's
+// last chunk takes from the next row meet weights zeroed by keep_bytes.
 template <class C, bool ALIGNED, int KIND, bool PLANES>
 struct Plan {
+    static constexpr bool CONV_ANY = !ALIGNED && KIND == KIND_CONV3X3;
+    static_assert(C::NT % C::CPR == 0, "a thread's chunks share one column of the tile");
     rsrc_t rX, rW;
     uint32_t offA[C::A_LOADS];   // linear: byte offset at k = kb; conv: pixel base
-    uint32_t offB[C::B_LOADS];
+    uint32_t offB[C::B_LOADS];   // byte offset at k = kb; byte-aligned conv: row base
     int hA[C::A_LOADS], wA[C::A_LOADS];   // conv: pixel coordinates
     int kend;                             // end of the K range (bytes)
+    bool tail;                            // byte-aligned operands: rows end inside a chunk
 
     __device__ __forceinline__ void init(const LayerDesc &d, int m0, int n0, int kb, int ke,
                                          int tid)
@@ -274,6 +325,46 @@ struct Plan {
                                       : kOOB;
                 }
             }
+        } else {
+            Window w;
+            tail = ((CONV_ANY ? d.C : d.K) & 15) != 0;
+            if constexpr (KIND == KIND_CONV3X3) {
+                // Pixels that the tile's taps touch.
+                const int p0 = max(0, m0 - d.Wd - 1);
+                w.init(d.X, d.H * d.Wd, p0, C::BM + 2 * d.Wd + 2, d.C);
+                rX = w.r;
+#pragma unroll
+                for (int i = 0; i < C::A_LOADS; ++i) {
+                    const int m = m0 + (tid + i * C::NT) / C::CPR;
+                    const bool ok = m < d.M;
+                    const int h = ok ? m / d.Wd : -(1 << 20);
+                    hA[i] = h;
+                    wA[i] = ok ? m - h * d.Wd : -(1 << 20);
+                    offA[i] = w.lead + (ok ? (uint32_t)(m - p0) * (uint32_t)d.C : 0u);
+                }
+            } else if constexpr (KIND == KIND_LINEAR) {
+                w.init(d.X, d.M, m0, C::BM, d.K);
+                rX = w.r;
+#pragma unroll
+                for (int i = 0; i < C::A_LOADS; ++i) {
+                    const int id = tid + i * C::NT;
+                    const int m = id / C::CPR, c = id % C::CPR;
+                    offA[i] = m0 + m < d.M
+                                  ? w.lead + (uint32_t)m * (uint32_t)d.K + (uint32_t)(kb + 16 * c)
+                                  : kOOB;
+                }
+            }
+            if constexpr (!PLANES && C::B_LOADS > 0) {
+                w.init(d.W, d.N, n0, C::BN, d.K);
+                rW = w.r;
+#pragma unroll
+                for (int i = 0; i < C::B_LOADS; ++i) {
+                    const int id = tid + i * C::NT;
+                    const int n = id / C::CPR, c = id % C::CPR;
+                    const uint32_t row = w.lead + (uint32_t)n * (uint32_t)d.K;
+                    offB[i] = n0 + n >= d.N ? kOOB : CONV_ANY ? row : row + (uint32_t)(kb + 16 * c);
+                }
+            }
         }
     }
 
@@ -306,56 +397,91 @@ struct Plan {
 // its LDS store.
 template <class C, bool ALIGNED, int KIND, bool PLANES>
 struct Regs {
-    v4i a[C::A_LOADS];
-    v4i b[C::B_LOADS];
+    static constexpr bool CONV_ANY = !ALIGNED && KIND == KIND_CONV3X3;
+    static constexpr bool A_ANY = !ALIGNED && KIND != KIND_CONV3X3_BYTES;
+    static constexpr bool B_ANY = !ALIGNED && !PLANES;
+    Chunk5 a[C::A_LOADS];        // hi only for byte-aligned operands
+    Chunk5 b[C::B_LOADS];
+    int k0;                      // first byte of the K tile
+    // Byte-aligned conv: the chunk column's offsets from a pixel and from a
+    // weight row.
+    uint32_t da, db;
+    int valid;                   // byte-aligned weights: bytes of a chunk before its row's end
 
     // Loads the K tile at absolute byte k0 = kb + kt.
     __device__ __forceinline__ void load(const Plan<C, ALIGNED, KIND, PLANES> &p,
-                                         const LayerDesc &d, int m0, int n0, int k0, uint32_t kt,
+                                         const LayerDesc &d, int m0, int n0, int k, uint32_t kt,
                                          int tid)
     {
+        k0 = k;
+        const int kbyte = k0 + 16 * (tid % C::CPR);
+        int tr = 0, ts = 0;
+        if constexpr (CONV_ANY) {
+            // K runs over 9 taps of C rounded up to 16 channels, so that no
+            // chunk crosses a tap; the channels past C meet zero weights.
+            const int C16 = (d.C + 15) & ~15;
+            const int tap = kbyte / C16, ci = kbyte - tap * C16;
+            tr = tap / 3;
+            ts = tap - 3 * tr;
+            da = (uint32_t)(((tr - 1) * d.Wd + (ts - 1)) * d.C + ci);
+            db = (uint32_t)(tap * d.C + ci);
+            valid = d.C - ci;
+        } else if constexpr (B_ANY) {
+            valid = p.kend - kbyte;
+        }
 #pragma unroll
         for (int i = 0; i < C::A_LOADS; ++i) {
             const int id = tid + i * C::NT;
             const int r = id / C::CPR, c = id % C::CPR;
-            if constexpr (!ALIGNED) {
-                if constexpr (KIND == KIND_CONV3X3)
-                    a[i] = load_conv_any(d, m0 + r, k0 + 16 * c);
-                else
-                    a[i] = load_rowmajor_any(d.X, d.M, d.K, m0 + r, k0 + 16 * c);
-            } else if constexpr (KIND == KIND_CONV3X3) {
-                a[i] = p.conv_chunk(d, i, k0, c);
-            } else {
-                a[i] = ld16(p.rX, p.offA[i] + kt);
-            }
+            if constexpr (CONV_ANY) {
+                const bool ok = (unsigned)(p.hA[i] + tr - 1) < (unsigned)d.H &&
+                                (unsigned)(p.wA[i] + ts - 1) < (unsigned)d.Wd;
+                a[i].load(p.rX, ok ? p.offA[i] + da : kOOB);
+            } else if constexpr (A_ANY)
+                a[i].load(p.rX, p.offA[i] + kt);
+            else if constexpr (!ALIGNED)
+                a[i].lo = load_conv_bytes(d, m0 + r, k0 + 16 * c);
+            else if constexpr (KIND == KIND_CONV3X3)
+                a[i].lo = p.conv_chunk(d, i, k0, c);
+            else
+                a[i].lo = ld16(p.rX, p.offA[i] + kt);
         }
 #pragma unroll
         for (int i = 0; i < C::B_LOADS; ++i) {
             const int id = tid + i * C::NT;
             const int r = id / C::CPR, c = id % C::CPR;
             if constexpr (PLANES)
-                b[i] = load_planes(d.P, d.N, d.K, d.bits, n0 + r, k0 + 16 * c);
-            else if constexpr (!ALIGNED)
-                b[i] = load_rowmajor_any(d.W, d.N, d.K, n0 + r, k0 + 16 * c);
+                b[i].lo = load_planes(d.P, d.N, d.K, d.bits, n0 + r, k0 + 16 * c);
+            else if constexpr (B_ANY)
+                b[i].load(p.rW, kbyte < p.kend ? p.offB[i] + (CONV_ANY ? db : kt) : kOOB);
             else
-                b[i] = ld16(p.rW, k0 + 16 * c < p.kend ? p.offB[i] + kt : kOOB);
+                b[i].lo = ld16(p.rW, k0 + 16 * c < p.kend ? p.offB[i] + kt : kOOB);
         }
     }
 
-    __device__ __forceinline__ void store(v4i *sA, v4i *sB, uint32_t wmask, int tid) const
+    __device__ __forceinline__ void store(const Plan<C, ALIGNED, KIND, PLANES> &p, v4i *sA,
+                                          v4i *sB, uint32_t wmask, int tid) const
     {
         const int msk = (int)wmask;
 #pragma unroll
         for (int i = 0; i < C::A_LOADS; ++i) {
             const int id = tid + i * C::NT;
             const int r = id / C::CPR, c = id % C::CPR;
-            sA[r * C::CPR + swz<C::CPR>(r, c)] = a[i];
+            if constexpr (A_ANY)
+                sA[r * C::CPR + swz<C::CPR>(r, c)] = a[i].bytes(p.offA[i] + (CONV_ANY ? da : 0u));
+            else
+                sA[r * C::CPR + swz<C::CPR>(r, c)] = a[i].lo;
         }
 #pragma unroll
         for (int i = 0; i < C::B_LOADS; ++i) {
             const int id = tid + i * C::NT;
             const int r = id / C::CPR, c = id % C::CPR;
-            v4i v = b[i];
+            v4i v = b[i].lo;
+            if constexpr (B_ANY) {
+                v = b[i].bytes(p.offB[i] + (CONV_ANY ? db : 0u));
+                if (p.tail)
+                    v = keep_bytes(v, valid);
+            }
             if constexpr (!PLANES) {
                 v.x &= msk;
                 v.y &= msk;
@@ -436,7 +562,7 @@ __device__ __forceinline__ void kloop(const LayerDesc &d, uint32_t wmask, int m0
                     read(stage, kk + 1, fa[(kk + 1) & 1], fb[(kk + 1) & 1]);
                     mfmas(fa[kk & 1], fb[kk & 1]);
                     if (kk == WRITE_KK) {
-                        ring[u].store(smA + (stage ^ 1) * SA, smB + (stage ^ 1) * SB, wmask, tid);
+                        ring[u].store(plan, smA + (stage ^ 1) * SA, smB + (stage ^ 1) * SB, wmask, tid);
                         if (t + 1 + C::PF < nk) {
                             const uint32_t off = (uint32_t)(t + 1 + C::PF) * C::BK;
                             ring[u].load(plan, d, m0, n0, kb + (int)off, off, tid);
@@ -510,7 +636,7 @@ __device__ __forceinline__ void mainloop(const LayerDesc &d, uint32_t wmask, int
 
     // Prologue: tile 0 into stage 0, tiles 1 .. PF into the ring.
     ring[0].load(plan, d, m0, n0, kb, 0u, tid);
-    ring[0].store(smA, smB, wmask, tid);
+    ring[0].store(plan, smA, smB, wmask, tid);
 #pragma unroll
     for (int u = 0; u < C::PF; ++u)
         if (1 + u < nk)
@@ -801,7 +927,8 @@ __global__ void __launch_bounds__(C::NT, C::OCC) k_masked_gemm(LayerDesc d)
     tile_coords(xcd_remap(blockIdx.x, gridDim.x), d.tiles_m, d.tiles_n, tm, tn);
     const int m0 = tm * C::BM, n0 = tn * C::BN;
     v16i acc[C::FM][C::FN];
-    mainloop<C, ALIGNED, KIND, PLANES>(d, keep_mask_dword(d.bits), m0, n0, 0, d.K, acc, smA,
+    const int ke = KIND == KIND_CONV3X3 && !ALIGNED ? 9 * ((d.C + 15) & ~15) : d.K;
+    mainloop<C, ALIGNED, KIND, PLANES>(d, keep_mask_dword(d.bits), m0, n0, 0, ke, acc, smA,
                                        smB);
     epilogue<C>(d, m0, n0, acc, d.bits, reinterpret_cast<char *>(smA));
 }
@@ -929,7 +1056,7 @@ k_masked_gemm_persistent(const LayerDesc *__restrict__ descs, int L, int total, 
         const int nk = (d.K + C::BK - 1) / C::BK;
         const uint32_t wmask = keep_mask_dword(bits);
         __syncthreads();                            // no wave still reads the previous tile's LDS
-        ring[0].store(smA, smB, wmask, tid);
+        ring[0].store(plan, smA, smB, wmask, tid);
         // Unconditional, so that no slot is live around the tile loop: a
         // tile past K reads zero weights through the buffer bounds and is
         // never consumed.
@@ -1014,9 +1141,12 @@ hipError_t launch_single_cfg(const LayerDesc &din, bool aligned, hipStream_t str
     if (d.kind == KIND_CONV3X3) {
         if (aligned)
             hipLaunchKernelGGL((k_masked_gemm<C, true, KIND_CONV3X3, false>), g, b, 0, stream, d);
-        else
+        else if ((C::BM + 2LL * d.Wd + 2) * d.C < (1LL << 31) - 8)
             hipLaunchKernelGGL((k_masked_gemm<C, false, KIND_CONV3X3, false>), g, b, 0, stream,
                                d);
+        else    // a tile's pixels past a 32-bit window
+            hipLaunchKernelGGL((k_masked_gemm<C, false, KIND_CONV3X3_BYTES, false>), g, b, 0,
+                               stream, d);
     } else if (aligned) {
         hipLaunchKernelGGL((k_masked_gemm<C, true, KIND_LINEAR, false>), g, b, 0, stream, d);
     } else {

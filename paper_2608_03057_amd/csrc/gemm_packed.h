@@ -133,7 +133,7 @@ __device__ __forceinline__ void mainloop_packed(const LayerDesc &d, uint32_t wma
     // Prologue: activation tile 0 into stage 0, tiles 1 .. PF into the ring,
     // weight tile 0 into registers.
     ring[0].load(plan, d, m0, n0, 0, 0u, tid);
-    ring[0].store(sm, nullptr, wmask, tid);
+    ring[0].store(plan, sm, nullptr, wmask, tid);
 #pragma unroll
     for (int u = 0; u < PF; ++u)
         if (1 + u < nk)
@@ -164,7 +164,7 @@ __device__ __forceinline__ void mainloop_packed(const LayerDesc &d, uint32_t wma
                             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                     }
                     if (kk == WRITE_KK) {
-                        ring[u].store(sm + (stage ^ 1) * SA, nullptr, wmask, tid);
+                        ring[u].store(plan, sm + (stage ^ 1) * SA, nullptr, wmask, tid);
                         if (t + 1 + PF < nk) {
                             const uint32_t off = (uint32_t)(t + 1 + PF) * C::BK;
                             ring[u].load(plan, d, m0, n0, (int)off, off, tid);
@@ -253,7 +253,7 @@ hipError_t launch_packed_single(const LayerDesc &din, bool aligned, hipStream_t 
         if (aligned)
             hipLaunchKernelGGL((k_gemm_packed<C, true, KIND_CONV3X3>), g, b, 0, stream, d);
         else
-            hipLaunchKernelGGL((k_gemm_packed<C, false, KIND_CONV3X3>), g, b, 0, stream, d);
+            hipLaunchKernelGGL((k_gemm_packed<C, false, KIND_CONV3X3_BYTES>), g, b, 0, stream, d);
     } else if (aligned) {
         hipLaunchKernelGGL((k_gemm_packed<C, true, KIND_LINEAR>), g, b, 0, stream, d);
     } else {

@@ -206,14 +206,17 @@ int pick_packed_grouped_tile(const tasq_opts *o)
 // tiles (8 waves, BK 128) from 140 tiles up, 128x128 tiles while they give
 // 200 tiles, 64x64 tiles below that so that more workgroups cover the 256
 // compute units.
-int pick_tile(const tasq_opts *o, long long M, long long N)
+// A conv on byte-aligned operands takes no 256x256 tiles: its chunks' taps
+// and shifts need more registers than that tile leaves (96x96 pixels 650 ->
+// 650: 93.8 us with 128x128 tiles, 152 with 256x256, 95.9 with 64x64).
+int pick_tile(const tasq_opts *o, long long M, long long N, bool any_conv = false)
 {
     const int f = forced_tile(o);
     if (f >= 0)
         return f;
     const long long t256 = ((M + 255) / 256) * ((N + 255) / 256);
     const long long t128 = ((M + 127) / 128) * ((N + 127) / 128);
-    if (t256 >= 140)
+    if (t256 >= 140 && !any_conv)
         return tasq::TILE_256x256_K128_W8_PF1;
     if (t128 >= 200)
         return tasq::TILE_128x128_K128_W4_PF2;
@@ -370,6 +373,11 @@ enum WeightSrc { SRC_NONE = 0, SRC_ROWS, SRC_PACKED, SRC_PLANES };
 //     72.5 / 71.0, SANA GLU-up (704) 145.4 / 133.4; SDXL-Turbo A-QKV (128)
 //     17.8 / 18.4, B-QKV (60) 17.9 / 21.6, B-ff-down (20) 30.6 / 33.9, the
 //     3x3 conv (20) 69.4 / 71.5, 256x1152x1152 (5) 10.6 / 12.1;
+//   * on byte-aligned activations (a K that is no multiple of 16, an odd
+//     address) a linear layer takes the packed copy, whose weights need no
+//     shifts (rows / packed: 4942x861 -> 640 15.6 / 12.4, 4096x2241 -> 2240
+//     48.1 / 39.1), and a conv the rows, because the packed K order lets a
+//     chunk cross taps (20x30 1275 -> 1280: 65 against more than 1000);
 //   * a schedule takes the rows, whose grouped step runs as the persistent
 //     launch: 4.23 ms per denoising step of the 28-block PixArt-shaped
 //     schedule against 4.59 ms for the grouped packed-weight launch.
@@ -395,6 +403,8 @@ WeightSrc weight_source(const LayerDesc &d, const tasq_opts *o, bool any_below8,
     if (packed && rows && !skinny_shape(d)) {
         if (in_schedule)
             return aligned16(d.W) ? SRC_ROWS : SRC_PACKED;
+        if (!x_aligned(d))
+            return linear ? SRC_PACKED : SRC_ROWS;
         const long long tiles = (long long)((d.M + 255) / 256) * ((d.N + 255) / 256);
         return tiles > kComputeUnits / 2 ? SRC_PACKED : SRC_ROWS;
     }
@@ -479,7 +489,8 @@ int launch_layer(const LayerDesc &d, const tasq_opts *o, hipStream_t stream,
             if (e == hipSuccess)
                 e = tasq::launch_split_finish(d, part, splits, stream);
         } else {
-            e = tasq::tile_ops(pick_tile(o, d.M, d.N)).single(d, aligned, stream);
+            const bool any_conv = !aligned && d.kind == tasq::KIND_CONV3X3;
+            e = tasq::tile_ops(pick_tile(o, d.M, d.N, any_conv)).single(d, aligned, stream);
         }
     }
     return e == hipSuccess ? TASQ_OK : TASQ_ERR_HIP;

@@ -7,7 +7,9 @@
 
 namespace tasq {
 
-enum : int { KIND_LINEAR = 0, KIND_CONV3X3 = 1 };
+// KIND_CONV3X3_BYTES is a kernel's form of a conv, never a layer's kind: its
+// activations gathered byte by byte.
+enum : int { KIND_LINEAR = 0, KIND_CONV3X3 = 1, KIND_CONV3X3_BYTES = 2 };
 
 // One masked GEMM as the kernels see it.  For a grouped schedule launch an
 // array of these lives in device memory; single calls pass one by value.
