@@ -191,3 +191,28 @@ def test_auto_schedule_streams_planes():
             ra, ry = oracle.masked_linear(X, want, SX, sw, b)
             check_outputs(d["acc"], d["y"], ra, ry, SX, sw, None,
                           f"layer {i} packed={with_packed} b={b}")
+
+
+@pytest.mark.parametrize("L", [1, 19, 20, 21, 40, 41, 42])
+@pytest.mark.parametrize("M", [5, 70])
+def test_schedule_layer_list_upload(L, M):
+    """Layer lists on both sides of the sizes at which the upload takes one
+    launch, two, or a copy (3584 bytes each): every layer runs at its own b
+    on its own operands."""
+    rng = np.random.default_rng(900 + L)
+    S = 3
+    table = torch.from_numpy(rng.integers(1, 9, (L, S)).astype(np.uint8))
+    layers, keep = [], []
+    for l in range(L):
+        N, K = 32 + 16 * (l % 3), 128 + 16 * (l % 2)
+        X, W, sw, _ = inputs.random_case(9000 + 50 * L + l, M, N, K)
+        d = (X.to(DEV), W.to(DEV), sw.to(DEV), torch.empty((M, N), dtype=torch.int32, device=DEV))
+        layers.append(T.make_layer(d[0], d[1], 0.02, d[2], acc=d[3]))
+        keep.append((X, W, sw, d))
+    ws = torch.empty(T.schedule_workspace_bytes(layers), dtype=torch.uint8, device=DEV)
+    for s in range(S):
+        T.run_schedule(layers, table, S, S, s, s + 1, workspace=ws)
+        torch.cuda.synchronize()
+        for l, (X, W, sw, d) in enumerate(keep):
+            ra, _ = oracle.masked_linear(X, W, 0.02, sw, int(table[l, s]))
+            assert np.array_equal(d[3].cpu().numpy(), np.asarray(ra)), (L, M, s, l)
