@@ -216,3 +216,29 @@ def test_schedule_layer_list_upload(L, M):
         for l, (X, W, sw, d) in enumerate(keep):
             ra, _ = oracle.masked_linear(X, W, 0.02, sw, int(table[l, s]))
             assert np.array_equal(d[3].cpu().numpy(), np.asarray(ra)), (L, M, s, l)
+
+
+@pytest.mark.parametrize("have", ["all", "no planes in one layer", "rows only in one layer"])
+def test_weight_stream_of_mixed_copies(have):
+    """A weight-streaming schedule in which AUTO would read different copies
+    in different layers (b = 8 in every stage of one, below 8 in the others;
+    copies missing in one) computes every layer at its own b."""
+    table = torch.tensor([[8, 8], [5, 3], [8, 2]], dtype=torch.uint8)
+    layers, keep = [], []
+    for l, (M, N, K) in enumerate([(16, 70, 144), (9, 32, 1040), (33, 100, 256)]):
+        X, W, sw, _ = inputs.random_case(9900 + l, M, N, K)
+        d = [X.to(DEV), W.to(DEV), sw.to(DEV), torch.empty((M, N), dtype=torch.int32, device=DEV)]
+        copies = dict(packed=T.pack_weights(d[1]), planes=T.pack_planes(d[1]))
+        if l == 1 and have != "all":
+            copies.pop("planes")
+            if have.startswith("rows"):
+                copies.pop("packed")
+        layers.append(T.make_layer(d[0], d[1], 0.02, d[2], acc=d[3], **copies))
+        keep.append((X, W, sw, d, copies))
+    ws = torch.empty(T.schedule_workspace_bytes(layers), dtype=torch.uint8, device=DEV)
+    for s in range(2):
+        T.run_schedule(layers, table, 2, 2, s, s + 1, workspace=ws)
+        torch.cuda.synchronize()
+        for l, (X, W, sw, d, _) in enumerate(keep):
+            ra, _ = oracle.masked_linear(X, W, 0.02, sw, int(table[l, s]))
+            assert np.array_equal(d[3].cpu().numpy(), np.asarray(ra)), (have, s, l)
