@@ -23,11 +23,11 @@
 //     segments.
 #pragma once
 
+#include "rows.h"
 #include "tasq_internal.h"
 
 namespace tasq {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -76,26 +76,6 @@ __device__ __forceinline__ int swz(int r, int c)
         return c ^ (((r >> 1) ^ (r >> 3)) & 3);
 }
 
-// ---------------------------------------------------------------- buffers
-
-// Raw buffer resources: a load whose byte offset is at or past num_records
-// returns zero and such a store is dropped, which bounds every access to
-// its operand without per-element checks.  Offsets are 32-bit; the host
-// keeps every operand below 2 GiB and kOOB marks a lane with nothing to do.
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-constexpr uint32_t kOOB = 0x80000000u;
-
-__device__ __forceinline__ rsrc_t make_rsrc(const void *p, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)bytes,
-                                             0x00020000);
-}
-
-__device__ __forceinline__ v4i ld16(rsrc_t r, uint32_t off)
-{
-    return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-}
-
 __device__ __forceinline__ v2i ld8(rsrc_t r, uint32_t off)
 {
     return __builtin_bit_cast(v2i, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
@@ -119,70 +99,6 @@ __device__ __forceinline__ void st32_cached(rsrc_t r, uint32_t off, uint32_t v)
 __device__ __forceinline__ v4i zero4() { return v4i{0, 0, 0, 0}; }
 
 // ------------------------------------------------- fallback (unaligned) loads
-
-// Rows of an int8 matrix at any byte alignment.  A 16-byte chunk at byte o of
-// the rows' window is taken as the five aligned dwords from o & ~3 on and
-// funnel-shifted into place (four v_alignbyte_b32) on its way to LDS.  The
-// window starts at the dword holding the first byte and ends with the dword
-// holding the last one, so every dword it reads holds a byte of the matrix;
-// the others are dropped by the buffer bounds.  It is set per output tile,
-// so the matrix itself may exceed the 2 GiB of a buffer offset.
-//
-// Bound by instruction issue and latency like the aligned path: the extra
-// dword load and shifts hide behind the matrix work of the other waves.
-// A call in a row of calls, against byte-by-byte loads (sixteen per chunk):
-// 777x1153 -> 1111 12.6 us (62.5 before, both with 64x64 tiles), 8192x1151 ->
-// 3456 64.2 us (361.7), a 20x30 conv 1275 -> 1280 64.9 us (1217).
-struct Window {
-    rsrc_t r;
-    uint32_t lead;              // bytes before the first row in its dword
-
-    __device__ __forceinline__ void init(const int8_t *base, int rows, int first, int count,
-                                         int K)
-    {
-        const int8_t *p = base + (size_t)first * (size_t)K;
-        lead = (uint32_t)(reinterpret_cast<uintptr_t>(p) & 3u);
-        const int n = min(rows - first, count);
-        const uint32_t bytes = n > 0 ? lead + (uint32_t)n * (uint32_t)K : 0u;
-        r = make_rsrc(p - lead, (bytes + 3u) & ~3u);
-    }
-};
-
-struct Chunk5 {
-    v4i lo;
-    uint32_t hi;
-
-    __device__ __forceinline__ void load(rsrc_t r, uint32_t off)
-    {
-        lo = ld16(r, off & ~3u);
-        hi = __builtin_amdgcn_raw_buffer_load_b32(r, (off & ~3u) + 16u, 0, 0);
-    }
-
-    // The 16 bytes from byte off % 4 of the five dwords on.
-    __device__ __forceinline__ v4i bytes(uint32_t off) const
-    {
-        const uint32_t a = (uint32_t)lo.x, b = (uint32_t)lo.y, c = (uint32_t)lo.z,
-                       d = (uint32_t)lo.w;
-        return v4i{(int)__builtin_amdgcn_alignbyte(b, a, off),
-                   (int)__builtin_amdgcn_alignbyte(c, b, off),
-                   (int)__builtin_amdgcn_alignbyte(d, c, off),
-                   (int)__builtin_amdgcn_alignbyte(hi, d, off)};
-    }
-};
-
-// Keeps the first `valid` bytes of a chunk.
-__device__ __forceinline__ v4i keep_bytes(v4i v, int valid)
-{
-    auto mask = [&](int w) {
-        const int n = valid - 4 * w;
-        return n >= 4 ? -1 : n <= 0 ? 0 : (1 << (8 * n)) - 1;
-    };
-    v.x &= mask(0);
-    v.y &= mask(1);
-    v.z &= mask(2);
-    v.w &= mask(3);
-    return v;
-}
 
 // Chunk of the implicit-GEMM activation of a 3x3 / pad 1 conv for any C,
 // byte by byte.  Only for what no window chunk serves: packed weights, whose

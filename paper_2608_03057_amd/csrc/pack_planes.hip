@@ -15,42 +15,62 @@
 // group's four bytes.  The words of channels n and n + 16 (f = 0, 1) sit side
 // by side, so the weight-streaming kernel reads both with one 8-byte load.
 // Words of channels past N and codes past K are zero.
+#include "rows.h"
 #include "tasq_internal.h"
 
 namespace tasq {
 
-// One thread per word position (nb, kb, r, w, f): reads the 32 codes it
-// covers and emits their 8 plane words.
-__global__ void k_pack_planes(const int8_t *__restrict__ W, int N, int K, int KB,
-                              long long positions, uint32_t *__restrict__ planes)
+// One wave per (32-channel block, K block), two word positions (r, w, f) per
+// lane: a position's 32 codes are two chunks, and a plane's bits of four
+// codes are one dword rotated to their group and masked, so a group costs
+// one rotate and one AND-OR per plane (nine instructions; bit by bit it was
+// about a hundred).  Bound by memory (@@PP@@).
+__global__ void __launch_bounds__(256) k_pack_planes(const int8_t *__restrict__ W, int N, int K,
+                                                     int KB, int blocks,
+                                                     uint32_t *__restrict__ planes)
 {
-    for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < positions;
-         idx += (long long)gridDim.x * blockDim.x) {
-        const int pos = (int)(idx & 127);          // 8 r + 2 w + f
+    const int blk = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (blk >= blocks)
+        return;
+    const int nb = blk / KB, kb = blk - nb * KB;
+    Window win;
+    win.init(W, N, 32 * nb, 32, K);
+    Chunk5 c[2][2];
+    uint32_t off[2];
+    int k0[2];
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+        const int pos = (threadIdx.x & 63) + 64 * v;    // 8 r + 2 w + f
         const int f = pos & 1, w = (pos >> 1) & 3, r = pos >> 3;
-        const long long blk = idx >> 7;            // nb * KB + kb
-        const int kb = (int)(blk % KB);
-        const long long nb = blk / KB;
-        const long long n = 32 * nb + 16 * f + r;
-        const int h = w >> 1, t = w & 1;
+        const int row = 16 * f + r;
+        k0[v] = 128 * kb + 64 * (w & 1) + 16 * (w >> 1);
+        off[v] = win.lead + (uint32_t)row * (uint32_t)K + (uint32_t)k0[v];
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl)                  // the word's two sub-steps
+            c[v][sl].load(win.r, 32 * nb + row < N && k0[v] + 32 * sl < K ? off[v] + 32u * sl
+                                                                          : kOOB);
+    }
+    uint32_t *out = planes + ((size_t)nb * 8 * (size_t)KB + (size_t)kb) * 128 + (threadIdx.x & 63);
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
         uint32_t pw[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (n < N) {
-            const int8_t *row = W + (size_t)n * (size_t)K;
-            for (int e = 0; e < 32; ++e) {
-                const int sl = e >> 4;             // which of the word's two sub-steps
-                const int i = (e >> 2) & 3, c = e & 3;
-                const int j = kb * 128 + 32 * (2 * t + sl) + 16 * h + 4 * i + c;
-                const uint32_t v = j < K ? (uint32_t)(uint8_t)row[j] : 0u;
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl) {
+            const v4i x = keep_bytes(c[v][sl].bytes(off[v]), K - k0[v] - 32 * sl);
+            const uint32_t d[4] = {(uint32_t)x.x, (uint32_t)x.y, (uint32_t)x.z, (uint32_t)x.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
                 const int g = 4 * sl + i;
+                // rotate left by g: bit p of byte c moves to 8c + p + g
+                const uint32_t rot = __builtin_amdgcn_alignbit(d[i], d[i], (32 - g) & 31);
 #pragma unroll
                 for (int p = 0; p < 8; ++p)
-                    pw[p] |= ((v >> p) & 1u) << ((8 * c + g + p) & 31);
+                    pw[p] |= rot & (0x01010101u << ((p + g) & 7));
             }
         }
 #pragma unroll
         for (int p = 0; p < 8; ++p)
-            planes[((size_t)(nb * 8 + (7 - p)) * (size_t)KB + (size_t)kb) * 128 + (size_t)pos] =
-                pw[p];
+            out[(size_t)(7 - p) * (size_t)KB * 128 + 64 * v] = pw[p];
     }
 }
 
@@ -58,12 +78,13 @@ hipError_t launch_pack_planes(const int8_t *W, int N, int K, uint32_t *planes,
                               hipStream_t stream)
 {
     const int KB = (K + 127) / 128;
-    const long long positions = (long long)((N + 31) / 32) * KB * 128;
-    long long blocks = (positions + 255) / 256;
-    if (blocks > 65535)
-        blocks = 65535;
-    hipLaunchKernelGGL(k_pack_planes, dim3((unsigned)blocks), dim3(256), 0, stream, W, N, K, KB,
-                       positions, planes);
+    const long long blocks = (long long)((N + 31) / 32) * KB;
+    if (blocks < 1)
+        return hipSuccess;
+    if (blocks > 0x7fffffffLL)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_pack_planes, dim3((unsigned)((blocks + 3) / 4)), dim3(256), 0, stream, W,
+                       N, K, KB, (int)blocks, planes);
     return hipGetLastError();
 }
 

@@ -6,49 +6,50 @@
 // KS = 4 * ceil(K / 128) units per 32-row block, and every byte past row N
 // or column K is zero.  The codes are copied unchanged: masking to b bits
 // happens in the kernels, so this one buffer serves every precision.
+#include "rows.h"
 #include "tasq_internal.h"
 
 namespace tasq {
 
-// One thread per 16-byte chunk of the packed buffer.
-__global__ void k_pack_weights(const int8_t *__restrict__ W, int N, int K, int KS,
-                               long long chunks, int8_t *__restrict__ packed)
+// One wave per (32-row block, 128-byte K block): four chunk loads per lane in
+// flight, then four 1 KB units written whole.  A copy in other order, bound
+// by memory; byte loads (sixteen per chunk) held it at 0.9 TB/s of reads and
+// writes (@@PW@@).
+__global__ void __launch_bounds__(256) k_pack_weights(const int8_t *__restrict__ W, int N, int K,
+                                                      int KB, int blocks,
+                                                      int8_t *__restrict__ packed)
 {
-    for (long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x; g < chunks;
-         g += (long long)gridDim.x * blockDim.x) {
-        const int l = (int)(g & 63);
-        const long long unit = g >> 6;
-        const int ks = (int)(unit % KS);
-        const int nb = (int)(unit / KS);
-        const int n = 32 * nb + (l & 31);
-        const int k0 = 32 * ks + 16 * (l >> 5);
-        uint32_t w[4] = {0, 0, 0, 0};
-        if (n < N) {
-            const int8_t *row = W + (size_t)n * (size_t)K;
-            for (int i = 0; i < 16; ++i)
-                if (k0 + i < K)
-                    w[i >> 2] |= (uint32_t)(uint8_t)row[k0 + i] << (8 * (i & 3));
-        }
-        uint32_t *out = reinterpret_cast<uint32_t *>(packed + g * 16);
-        out[0] = w[0];
-        out[1] = w[1];
-        out[2] = w[2];
-        out[3] = w[3];
-    }
+    const int blk = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (blk >= blocks)
+        return;
+    const int nb = blk / KB, kb = blk - nb * KB;
+    const int lane = threadIdx.x & 63, row = lane & 31;
+    Window w;
+    w.init(W, N, 32 * nb, 32, K);
+    const bool ok = 32 * nb + row < N;
+    const int k0 = 128 * kb + 16 * (lane >> 5);
+    const uint32_t off = w.lead + (uint32_t)row * (uint32_t)K + (uint32_t)k0;
+    Chunk5 c[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        c[u].load(w.r, ok && k0 + 32 * u < K ? off + 32u * u : kOOB);
+    v4i *out = reinterpret_cast<v4i *>(packed) + (size_t)blk * 256 + lane;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        out[64 * u] = keep_bytes(c[u].bytes(off), K - k0 - 32 * u);
 }
 
 hipError_t launch_pack_weights(const int8_t *W, int N, int K, int8_t *packed,
                                hipStream_t stream)
 {
-    const int KS = (K + 127) / 128 * 4;
-    const long long chunks = (long long)((N + 31) / 32) * KS * 64;
-    long long blocks = (chunks + 255) / 256;
-    if (blocks > 65535)
-        blocks = 65535;
+    const int KB = (K + 127) / 128;
+    const long long blocks = (long long)((N + 31) / 32) * KB;
     if (blocks < 1)
         return hipSuccess;
-    hipLaunchKernelGGL(k_pack_weights, dim3((unsigned)blocks), dim3(256), 0, stream, W, N, K, KS,
-                       chunks, packed);
+    if (blocks > 0x7fffffffLL)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_pack_weights, dim3((unsigned)((blocks + 3) / 4)), dim3(256), 0, stream,
+                       W, N, K, KB, (int)blocks, packed);
     return hipGetLastError();
 }
 
