@@ -19,6 +19,7 @@
 // batched form runs the passes of many tensors in few launches.
 #include <vector>
 
+#include "quant.h"
 #include "rows.h"
 #include "tasq_internal.h"
 
@@ -114,11 +115,31 @@ __device__ __forceinline__ void scale_of(uint32_t kmn, uint32_t kmx, float &alph
     }
 }
 
-__device__ __forceinline__ int8_t code_of(float x, float alpha, float z)
+// Codes of elements first, first + step, .. below n (vector part: groups of
+// four), div the division by alpha.
+template <class Div>
+__device__ __forceinline__ void act_codes(const float *__restrict__ x, long long n, long long n4,
+                                          int8_t *__restrict__ q, float z, long long first,
+                                          long long stride, const Div &div)
 {
-    float r = rintf(__fadd_rn(__fdiv_rn(x, alpha), z));
-    r = fminf(fmaxf(r, 0.0f), 255.0f);
-    return (int8_t)((int)r - 128);
+    auto code = [&](float v) { return rintf(__fadd_rn(div(v), z)); };
+    auto codes = [&](float4 v) { return pack_codes(code(v.x), code(v.y), code(v.z), code(v.w)); };
+    const float4 *x4 = reinterpret_cast<const float4 *>(x);
+    uint32_t *q4 = reinterpret_cast<uint32_t *>(q);
+    long long i = first;
+    for (; i + 3 * stride < n4; i += 4 * stride) {
+        float4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            v[u] = x4[i + u * stride];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            q4[i + u * stride] = codes(v[u]);
+    }
+    for (; i < n4; i += stride)
+        q4[i] = codes(x4[i]);
+    for (long long t = (n4 << 2) + first; t < n; t += stride)
+        q[t] = (int8_t)pack_codes(code(x[t]), 0.f, 0.f, 0.f);
 }
 
 // Every workgroup (g of Q) folds the G partial ranges (a few KB, cache
@@ -155,26 +176,12 @@ __device__ __forceinline__ void act_quantize(const float *__restrict__ x, long l
         params[1] = z;
     }
     const long long stride = (long long)Q * blockDim.x;
-    const float4 *x4 = reinterpret_cast<const float4 *>(x);
-    char4 *q4 = reinterpret_cast<char4 *>(q);
-    long long i = (long long)g * blockDim.x + threadIdx.x;
-    for (; i + 3 * stride < n4; i += 4 * stride) {
-        float4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            v[u] = x4[i + u * stride];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            q4[i + u * stride] = make_char4(code_of(v[u].x, alpha, z), code_of(v[u].y, alpha, z),
-                                            code_of(v[u].z, alpha, z), code_of(v[u].w, alpha, z));
-    }
-    for (; i < n4; i += stride) {
-        const float4 v = x4[i];
-        q4[i] = make_char4(code_of(v.x, alpha, z), code_of(v.y, alpha, z), code_of(v.z, alpha, z),
-                           code_of(v.w, alpha, z));
-    }
-    for (long long i = (n4 << 2) + (long long)g * blockDim.x + threadIdx.x; i < n; i += stride)
-        q[i] = code_of(x[i], alpha, z);
+    const long long first = (long long)g * blockDim.x + threadIdx.x;
+    const Divider div(alpha);
+    if (div.exact)
+        act_codes(x, n, n4, q, z, first, stride, div);
+    else
+        act_codes(x, n, n4, q, z, first, stride, [&](float v) { return __fdiv_rn(v, alpha); });
 }
 
 __global__ void __launch_bounds__(256) k_act_quantize(const float *__restrict__ x, long long n,

@@ -14,6 +14,7 @@
 //
 // Also the row sums of int8 activation codes, which the weight zero point
 // needs: sum_k x_hat w_hat_b = sw (sum_k x_hat W_b + (128 - z) sum_k x_hat).
+#include "quant.h"
 #include "tasq.h"
 #include "tasq_internal.h"
 
@@ -23,14 +24,6 @@
 namespace tasq {
 
 namespace {
-
-// fp32 code decision of value v (the order written in the header comment).
-__device__ __forceinline__ int8_t weight_code(float v, float alpha, float z)
-{
-    float f = floorf(__fadd_rn(__fdiv_rn(v, alpha), z));
-    f = fminf(fmaxf(f, 0.0f), 255.0f);
-    return (int8_t)((int)f - 128);
-}
 
 __device__ __forceinline__ void range_to_scale(float mn, float mx, float &alpha, float &z)
 {
@@ -43,10 +36,16 @@ __device__ __forceinline__ void range_to_scale(float mn, float mx, float &alpha,
     }
 }
 
-// Output channel n of one weight, by one wave: range, then codes (the row
-// read a second time, from L2); lane 0 writes the channel's alpha, z and
-// sw.  vec: W rows 16-byte aligned (K % 4 == 0 and W aligned) and Q rows
-// 4-byte aligned.
+// float4 of a row that a lane keeps in registers between its range and its
+// codes: rows of up to 64 * 4 * kRowKeep = 2048 weights are read once.
+constexpr int kRowKeep = 8;
+
+// Output channel n of one weight, by one wave: range, then codes; lane 0
+// writes the channel's alpha, z and sw.  Bound by the latency of the row's
+// loads at these row lengths, so all loads of the kept part are issued
+// before any is used; the rest of a longer row is streamed four loads at a
+// time and read a second time, from L2.  vec: W rows 16-byte aligned
+// (K % 4 == 0 and W aligned) and Q rows 4-byte aligned.
 __device__ __forceinline__ void quantize_row(const float *__restrict__ W, int K,
                                              int8_t *__restrict__ Q, float *__restrict__ alpha_out,
                                              float *__restrict__ z_out,
@@ -58,12 +57,44 @@ __device__ __forceinline__ void quantize_row(const float *__restrict__ W, int K,
     float mn = __builtin_huge_valf(), mx = -__builtin_huge_valf();
     const int K4 = vec ? K / 4 : 0;
     const float4 *w4 = reinterpret_cast<const float4 *>(w);
-    for (int i = lane; i < K4; i += 64) {
-        const float4 v = w4[i];
+    auto fold = [&](float4 v) {
         mn = fminf(fminf(mn, v.x), fminf(v.y, fminf(v.z, v.w)));
         mx = fmaxf(fmaxf(mx, v.x), fmaxf(v.y, fmaxf(v.z, v.w)));
+    };
+    float4 keep[kRowKeep];
+#pragma unroll
+    for (int u = 0; u < kRowKeep; ++u)
+        if (lane + 64 * u < K4)
+            keep[u] = w4[lane + 64 * u];
+    int i = lane + 64 * kRowKeep;
+    for (; i + 3 * 64 < K4; i += 4 * 64) {
+        float4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            v[u] = w4[i + 64 * u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            fold(v[u]);
     }
-    for (int k = 4 * K4 + lane; k < K; k += 64) {
+    for (; i < K4; i += 64)
+        fold(w4[i]);
+#pragma unroll
+    for (int u = 0; u < kRowKeep; ++u)
+        if (lane + 64 * u < K4)
+            fold(keep[u]);
+    int k = 4 * K4 + lane;
+    for (; k + 7 * 64 < K; k += 8 * 64) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            v[u] = w[k + 64 * u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            mn = fminf(mn, v[u]);
+            mx = fmaxf(mx, v[u]);
+        }
+    }
+    for (; k < K; k += 64) {
         mn = fminf(mn, w[k]);
         mx = fmaxf(mx, w[k]);
     }
@@ -73,14 +104,46 @@ __device__ __forceinline__ void quantize_row(const float *__restrict__ W, int K,
     }
     float alpha, z;
     range_to_scale(mn, mx, alpha, z);
-    auto code = [&](float v) -> int8_t { return weight_code(v, alpha, z); };
-    char4 *q4 = reinterpret_cast<char4 *>(q);
-    for (int i = lane; i < K4; i += 64) {
-        const float4 v = w4[i];
-        q4[i] = make_char4(code(v.x), code(v.y), code(v.z), code(v.w));
-    }
-    for (int k = 4 * K4 + lane; k < K; k += 64)
-        q[k] = code(w[k]);
+    auto write = [&](auto div) {
+        auto code = [&](float v) { return floorf(__fadd_rn(div(v), z)); };
+        auto codes = [&](float4 v) {
+            return pack_codes(code(v.x), code(v.y), code(v.z), code(v.w));
+        };
+        uint32_t *q4 = reinterpret_cast<uint32_t *>(q);
+#pragma unroll
+        for (int u = 0; u < kRowKeep; ++u)
+            if (lane + 64 * u < K4)
+                q4[lane + 64 * u] = codes(keep[u]);
+        int i = lane + 64 * kRowKeep;
+        for (; i + 3 * 64 < K4; i += 4 * 64) {
+            float4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                v[u] = w4[i + 64 * u];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                q4[i + 64 * u] = codes(v[u]);
+        }
+        for (; i < K4; i += 64)
+            q4[i] = codes(w4[i]);
+        int k = 4 * K4 + lane;
+        for (; k + 7 * 64 < K; k += 8 * 64) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                v[u] = w[k + 64 * u];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                q[k + 64 * u] = (int8_t)pack_codes(code(v[u]), 0.f, 0.f, 0.f);
+        }
+        for (; k < K; k += 64)
+            q[k] = (int8_t)pack_codes(code(w[k]), 0.f, 0.f, 0.f);
+    };
+    const Divider div(alpha);
+    if (div.exact)
+        write(div);
+    else
+        write([&](float v) { return __fdiv_rn(v, alpha); });
     if (lane == 0) {
         alpha_out[n] = alpha;
         z_out[n] = z;
