@@ -64,9 +64,10 @@ __host__ __device__ inline size_t packed_weight_bytes(int N, int K)
 // fragment of sub-step kk of tile t+1 is loaded into the same registers, so
 // each weight load has one whole K tile to land and only one K tile of
 // weights is held in registers.
-template <class C, bool ALIGNED, int KIND>
+template <class C, bool ALIGNED, int KIND, class Last>
 __device__ __forceinline__ void mainloop_packed(const LayerDesc &d, uint32_t wmask, int m0, int n0,
-                                                v16i (&acc)[C::FM][C::FN], v4i *sm)
+                                                v16i (&acc)[C::FM][C::FN], v4i *sm,
+                                                const Last &before_last)
 {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -81,8 +82,10 @@ __device__ __forceinline__ void mainloop_packed(const LayerDesc &d, uint32_t wma
         for (int j = 0; j < C::FN; ++j)
             acc[i][j] = v16i{};
     const int nk = (d.K + C::BK - 1) / C::BK;
-    if (nk <= 0)
+    if (nk <= 0) {
+        before_last();
         return;
+    }
 
     Plan<C, ALIGNED, KIND, false> plan;
     plan.init(d, m0, n0, 0, d.K, tid);
@@ -186,6 +189,7 @@ __device__ __forceinline__ void mainloop_packed(const LayerDesc &d, uint32_t wma
         }
     }
     // Last K tile.
+    before_last();
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
         if (kk + 1 < KK)
@@ -200,13 +204,16 @@ __device__ __forceinline__ void mainloop_packed(const LayerDesc &d, uint32_t wma
 template <class C, bool ALIGNED, int KIND>
 __global__ void __launch_bounds__(C::NT, C::OCC) k_gemm_packed(LayerDesc d)
 {
+    pin(d);
     __shared__ v4i sm[C::SM];
     int tm, tn;
     tile_coords(xcd_remap(blockIdx.x, gridDim.x), d.tiles_m, d.tiles_n, tm, tn);
     const int m0 = tm * C::BM, n0 = tn * C::BN;
     v16i acc[C::FM][C::FN];
-    mainloop_packed<C, ALIGNED, KIND>(d, keep_mask_dword(d.bits), m0, n0, acc, sm);
-    epilogue<C>(d, m0, n0, acc, d.bits, reinterpret_cast<char *>(sm));
+    ColLoads<C> cl;
+    mainloop_packed<C, ALIGNED, KIND>(d, keep_mask_dword(d.bits), m0, n0, acc, sm,
+                                      [&] { cols_request<C, true>(d, n0, d.bits, cl); });
+    epilogue<C>(d, m0, n0, acc, cl, reinterpret_cast<char *>(sm));
 }
 
 // Grouped step over every layer (see k_masked_gemm_grouped); every layer
@@ -218,26 +225,21 @@ k_gemm_packed_grouped(const LayerDesc *__restrict__ descs, int L, const uint8_t 
 {
     __shared__ v4i sm[C::SM];
     const int t = xcd_remap(blockIdx.x, gridDim.x);
-    int lo = 0, hi = L - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (descs[mid].tile_begin <= t)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    const LayerDesc d = descs[lo];
-    const int bits = table[d.layer * S + stage];
+    LayerDesc d = descs[find_segment(descs, L, t)];
+    pin(d);
+    const int bits = table_bits(table, d.layer * S + stage);
     const uint32_t wmask = keep_mask_dword(bits);
     int tm, tn;
     tile_coords(t - d.tile_begin + d.tile_first, d.tiles_m, d.tiles_n, tm, tn);
     const int m0 = tm * C::BM, n0 = tn * C::BN;
     v16i acc[C::FM][C::FN];
+    ColLoads<C> cl;
+    auto before_last = [&] { cols_request<C, true>(d, n0, bits, cl); };
     if (CONV && d.kind == KIND_CONV3X3)
-        mainloop_packed<C, true, KIND_CONV3X3>(d, wmask, m0, n0, acc, sm);
+        mainloop_packed<C, true, KIND_CONV3X3>(d, wmask, m0, n0, acc, sm, before_last);
     else
-        mainloop_packed<C, true, KIND_LINEAR>(d, wmask, m0, n0, acc, sm);
-    epilogue<C>(d, m0, n0, acc, bits, reinterpret_cast<char *>(sm));
+        mainloop_packed<C, true, KIND_LINEAR>(d, wmask, m0, n0, acc, sm, before_last);
+    epilogue<C>(d, m0, n0, acc, cl, reinterpret_cast<char *>(sm));
 }
 
 template <class C>

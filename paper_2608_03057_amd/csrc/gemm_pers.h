@@ -150,74 +150,6 @@ struct PersOperands {
     }
 };
 
-// The epilogue's per-column factors (as epilogue_cols in gemm_core.h), in
-// two parts: the loads, issued early and read with buffer loads (a
-// generic-pointer load would also count as an LDS access and be waited for
-// with every other memory request in flight), and the arithmetic, done when
-// the epilogue needs it, so that the loads' latency is not waited for at
-// the point of issue.
-template <class C>
-struct ColLoads {
-    float sw[C::FN], bias[C::FN], wz[C::FN];
-    int cs[C::FN];
-    float alpha, zx;
-};
-
-template <class C, bool EXTRAS = false>
-__device__ __forceinline__ void cols_request(const LayerDesc &d, int n0, int bits,
-                                             ColLoads<C> &cl)
-{
-    const int lane = threadIdx.x & 63;
-    const int wn = (threadIdx.x >> 6) % C::WAVES_N;
-    const uint32_t nb = (uint32_t)d.N * 4u;
-    const rsrc_t rsw = make_rsrc(d.sw, d.sw ? nb : 0u);
-    const rsrc_t rbias = make_rsrc(d.bias, d.bias ? nb : 0u);
-    const rsrc_t rcs = make_rsrc(d.colsums, d.act ? 8u * nb : 0u);
-    const rsrc_t ract = make_rsrc(d.act, d.act ? 8u : 0u);
-    cl.alpha = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ract, 0, 0, 0));
-    cl.zx = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ract, 4, 0, 0));
-#pragma unroll
-    for (int j = 0; j < C::FN; ++j) {
-        const int n = n0 + wn * C::WTN + j * 32 + (lane & 31);
-        const bool nok = n < d.N;
-        const uint32_t on = nok ? (uint32_t)n * 4u : kOOB;
-        cl.sw[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsw, on, 0, 0));
-        cl.bias[j] =
-            __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rbias, on, 0, 0));
-        cl.cs[j] = (int)__builtin_amdgcn_raw_buffer_load_b32(
-            rcs, nok ? ((uint32_t)(bits - 1) * (uint32_t)d.N + (uint32_t)n) * 4u : kOOB, 0, 0);
-        cl.wz[j] = 0.f;
-        if constexpr (EXTRAS) {
-            // weight zero points z_n, read only when the epilogue adds their term
-            const rsrc_t rwz = make_rsrc(d.wz, d.wz && d.y ? nb : 0u);
-            cl.wz[j] =
-                __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rwz, on, 0, 0));
-        }
-    }
-}
-
-template <class C, bool EXTRAS = false>
-__device__ __forceinline__ void cols_finish(const LayerDesc &d, int m0, int n0,
-                                            const ColLoads<C> &cl, EpiCols<C> &ec)
-{
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
-    const int mrow = m0 + wm * C::WTM + 4 * (lane >> 5);
-    const bool asym = d.act != nullptr;
-#pragma unroll
-    for (int j = 0; j < C::FN; ++j) {
-        const int n = n0 + wn * C::WTN + j * 32 + (lane & 31);
-        const bool nok = n < d.N;
-        ec.scale[j] = (asym ? cl.alpha : d.sx) * cl.sw[j];
-        ec.bias[j] = cl.bias[j];
-        ec.corr[j] = asym ? (128.0f - cl.zx) * (float)cl.cs[j] : 0.0f;
-        // (128 - z_n) times the column scale: the weight zero point's term
-        ec.wsc[j] = EXTRAS && d.wz && d.y ? (128.0f - cl.wz[j]) * ec.scale[j] : 0.f;
-        ec.base[j] = nok ? ((uint32_t)mrow * (uint32_t)d.N + (uint32_t)n) * 4u : kOOB;
-    }
-}
-
 // One workgroup per compute unit walks its XCD's run of work units (as in
 // k_masked_gemm_persistent).  g counts K tiles across the walk: K tile t of
 // the current tile is global K tile g0 + t, in activation stage (g0+t) % 3
@@ -251,11 +183,7 @@ k_masked_gemm_persistent_ds(const LayerDesc *__restrict__ descs, int L, int tota
     if (u >= uend)
         return;
 
-    auto bits_of = [&](int sg) {
-        const int idx = descs[sg].layer * S + stage;
-        const uint32_t w = reinterpret_cast<const uint32_t *>(table)[idx >> 2];
-        return (int)((w >> (8 * (idx & 3))) & 0xffu);
-    };
+    auto bits_of = [&](int sg) { return table_bits(table, descs[sg].layer * S + stage); };
     auto a_stage = [&](int g) { return smA + (g % pers::kAStages) * Ops::A_STAGE; };
     auto b_stage = [&](int g) {
         return reinterpret_cast<v4i *>(smB + (g & 1) * Ops::B_STAGE);

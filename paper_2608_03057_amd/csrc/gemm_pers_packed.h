@@ -116,11 +116,7 @@ k_gemm_packed_persistent(const LayerDesc *__restrict__ descs, int L, int total, 
     if (ubeg + jj >= uend)
         return;
 
-    auto bits_of = [&](int sg) {
-        const int idx = descs[sg].layer * S + stage;
-        const uint32_t w = reinterpret_cast<const uint32_t *>(table)[idx >> 2];
-        return (int)((w >> (8 * (idx & 3))) & 0xffu);
-    };
+    auto bits_of = [&](int sg) { return table_bits(table, descs[sg].layer * S + stage); };
     auto a_stage = [&](int g) { return sm + (g % ppk::kAStages) * A_STAGE; };
 
     // Compute position, weight request position (one K tile ahead) and
