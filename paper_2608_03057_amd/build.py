@@ -37,6 +37,7 @@ SOURCES = [
     "weight_quant.hip",
     "skinny.hip",
     "splitk.hip",
+    "kgroups.hip",
     "tiles.cpp",
     "cost.cpp",
     "tasq_api.cpp",

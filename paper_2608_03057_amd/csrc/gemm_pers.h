@@ -150,19 +150,40 @@ struct PersOperands {
     }
 };
 
+// The layers that a persistent launch walks: the device list of a schedule
+// step, or the one layer of a single call, which travels by value.
+struct StepLayers {
+    const LayerDesc *__restrict__ descs;
+    const uint8_t *__restrict__ table;
+    int L, S, stage;
+
+    __device__ __forceinline__ int find(int u) const { return find_segment(descs, L, u); }
+    __device__ __forceinline__ const LayerDesc &desc(int seg) const { return descs[seg]; }
+    __device__ __forceinline__ int bits(int seg) const
+    {
+        return table_bits(table, descs[seg].layer * S + stage);
+    }
+};
+
+struct OneLayer {
+    const LayerDesc &d;
+
+    __device__ __forceinline__ int find(int) const { return 0; }
+    __device__ __forceinline__ const LayerDesc &desc(int) const { return d; }
+    __device__ __forceinline__ int bits(int) const { return d.bits; }
+};
+
 // One workgroup per compute unit walks its XCD's run of work units (as in
 // k_masked_gemm_persistent).  g counts K tiles across the walk: K tile t of
 // the current tile is global K tile g0 + t, in activation stage (g0+t) % 3
 // and weight stage (g0+t) % 2; weight K tile t sits in register slot t % 2
 // from its load until its LDS store (both slots are empty at a tile
 // boundary, so the slots need not rotate across tiles).
-template <class C, bool EXTRAS>
-__global__ void __launch_bounds__(C::NT, C::OCC)
-k_masked_gemm_persistent_ds(const LayerDesc *__restrict__ descs, int L, int total, XcdRuns runs,
-                            const uint8_t *__restrict__ table, int S, int stage, int parties)
+template <class C, bool EXTRAS, class Layers>
+__device__ __forceinline__ void persistent_ds(const Layers &layers, const XcdRuns &runs,
+                                              int parties, char *sm)
 {
     using Ops = PersOperands<C>;
-    __shared__ __attribute__((aligned(1024))) char sm[Ops::LDS];
     char *const smA = sm;
     char *const smB = sm + pers::kAStages * Ops::A_STAGE;
     constexpr int NX = 8;
@@ -183,7 +204,6 @@ k_masked_gemm_persistent_ds(const LayerDesc *__restrict__ descs, int L, int tota
     if (u >= uend)
         return;
 
-    auto bits_of = [&](int sg) { return table_bits(table, descs[sg].layer * S + stage); };
     auto a_stage = [&](int g) { return smA + (g % pers::kAStages) * Ops::A_STAGE; };
     auto b_stage = [&](int g) {
         return reinterpret_cast<v4i *>(smB + (g & 1) * Ops::B_STAGE);
@@ -203,19 +223,19 @@ k_masked_gemm_persistent_ds(const LayerDesc *__restrict__ descs, int L, int tota
         ops.load_b(ring[1], t0 + 1);
     };
 
-    int seg = find_segment(descs, L, u);
+    int seg = layers.find(u);
     int m0, n0;
-    unit_coords<C>(descs[seg], u, m0, n0);
-    int bits = bits_of(seg);
+    unit_coords<C>(layers.desc(seg), u, m0, n0);
+    int bits = layers.bits(seg);
     int g0 = 0;                       // global K tile of the current tile's K tile 0
     bool first = true;
     {
-        const LayerDesc &d0 = descs[seg];
+        const LayerDesc &d0 = layers.desc(seg);
         ops.init(d0, m0, n0, tid);
         issue_first(0, 0);
     }
     for (;;) {
-        const LayerDesc &d = descs[seg];
+        const LayerDesc &d = layers.desc(seg);
         const int nk = (d.K + C::BK - 1) / C::BK;
         const uint32_t wmask = keep_mask_dword(bits);
 
@@ -334,12 +354,12 @@ k_masked_gemm_persistent_ds(const LayerDesc *__restrict__ descs, int L, int tota
         u += wgs;
         const bool more = u < uend;
         if (more) {
-            seg = find_segment(descs, L, u);
-            unit_coords<C>(descs[seg], u, m0, n0);
-            bits = bits_of(seg);
+            seg = layers.find(u);
+            unit_coords<C>(layers.desc(seg), u, m0, n0);
+            bits = layers.bits(seg);
             int t2 = tid;
             asm volatile("" : "+v"(t2));
-            ops.init(descs[seg], m0, n0, t2);
+            ops.init(layers.desc(seg), m0, n0, t2);
         }
         // With no next tile the same requests go out past K (zeros into free
         // stages and slots), so that the epilogue's waits see one count.
@@ -393,6 +413,29 @@ k_masked_gemm_persistent_ds(const LayerDesc *__restrict__ descs, int L, int tota
 }
 
 template <class C, bool EXTRAS>
+__global__ void __launch_bounds__(C::NT, C::OCC)
+k_masked_gemm_persistent_ds(const LayerDesc *__restrict__ descs, int L, int total, XcdRuns runs,
+                            const uint8_t *__restrict__ table, int S, int stage, int parties)
+{
+    __shared__ __attribute__((aligned(1024))) char sm[PersOperands<C>::LDS];
+    persistent_ds<C, EXTRAS>(StepLayers{descs, table, L, S, stage}, runs, parties, sm);
+}
+
+// A single layer of at least about half a tile per compute unit, whose K loop
+// gets the same two K tiles of prefetch and whose tile ends overlap as in a
+// step.  us, one workgroup per tile / this walk: 4096x2240 -> 2240 36.4 / 33.8,
+// 8192x1152 -> 3456 50.9 / 46.9, 4096x2240 -> 11200 113.7 / 104.6, 8192x8192 ->
+// 8192 438 / 412 (2.67 POP/s).
+template <class C, bool EXTRAS>
+__global__ void __launch_bounds__(C::NT, C::OCC) k_masked_gemm_ds(LayerDesc d, XcdRuns runs)
+{
+    __shared__ __attribute__((aligned(1024))) char sm[PersOperands<C>::LDS];
+    if constexpr (!EXTRAS)          // with them the scalar registers would not hold it all
+        pin(d);
+    persistent_ds<C, EXTRAS>(OneLayer{d}, runs, 1, sm);
+}
+
+template <class C, bool EXTRAS>
 hipError_t launch_persistent_ds_cfg(const LayerDesc *d_descs, int L, int total_tiles,
                                     const XcdRuns &runs, const uint8_t *d_table, int S, int stage,
                                     int wgs_per_xcd, int parties, hipStream_t stream)
@@ -406,10 +449,34 @@ hipError_t launch_persistent_ds_cfg(const LayerDesc *d_descs, int L, int total_t
     return hipGetLastError();
 }
 
+// One aligned linear layer as a persistent walk: the tiles cut evenly over
+// the 8 XCDs, 32 workgroups each.
+template <class C>
+hipError_t launch_single_ds(const LayerDesc &din, bool aligned, hipStream_t stream)
+{
+    if (!aligned || din.kind != KIND_LINEAR || din.K <= 0)
+        return launch_single_cfg<C>(din, aligned, stream);
+    LayerDesc d = din;
+    fill_tiles<C>(d);
+    const long long tiles = (long long)d.tiles_m * d.tiles_n;
+    if (tiles > 0x7fffffffLL)
+        return hipErrorInvalidValue;
+    d.tile_begin = d.tile_first = 0;
+    XcdRuns runs;
+    for (int x = 0; x <= 8; ++x)
+        runs.begin[x] = (int)(tiles * x / 8);
+    dim3 g(256), b(C::NT);
+    if (d.lr_T || d.wz)
+        hipLaunchKernelGGL((k_masked_gemm_ds<C, true>), g, b, 0, stream, d, runs);
+    else
+        hipLaunchKernelGGL((k_masked_gemm_ds<C, false>), g, b, 0, stream, d, runs);
+    return hipGetLastError();
+}
+
 #define TASQ_DEFINE_TILE_DS(NAME, CFG)                                                      \
     const TileOps &NAME()                                                                   \
     {                                                                                       \
-        static const TileOps ops = {{CFG::BM, CFG::BN, CFG::BK}, &launch_single_cfg<CFG>,   \
+        static const TileOps ops = {{CFG::BM, CFG::BN, CFG::BK}, &launch_single_ds<CFG>,    \
                                     &launch_planes_cfg<CFG>, &launch_grouped_cfg<CFG>,      \
                                     &launch_split_cfg<CFG>,                                 \
                                     &launch_persistent_ds_cfg<CFG, false>,                  \

@@ -177,10 +177,14 @@ int persistent_parties(const tasq_opts *o, int wgs_per_xcd)
 
 // Packed-weight tile of a single launch, from a sweep of every tile over the
 // DiT/UNet layer shapes with the Infinity Cache flushed before each launch:
-// the 256x256 tile once it gives at least 140 tiles (even half a wave of
-// 256x256 tiles beats 2-3 waves of smaller ones from about there), the
-// 4-wave 128x256 tile (two workgroups per CU) while it gives 200 tiles, and
-// 64x64 tiles below that.
+// the 256x256 tile for 140 tiles up to one per compute unit (even half a
+// round of 256x256 tiles beats 2-3 of smaller ones from about there) and for
+// the largest layers, the 4-wave 128x256 tile (two workgroups per CU, one's
+// stores under the other's matrix work) while it gives 200 tiles, and 64x64
+// tiles below that.  us, 128x256 / 256x256: 4096x2240 -> 2240 (144 tiles of
+// 256x256) 36.1 / 33.7, 8192x1152 -> 3456 (448) 42.1 / 49.7, 8192x1152 -> 4608
+// (576) 51.1 / 66.3, 4096x2240 -> 11200 (704) 109.3 / 115.4, 6278x11200 -> 3456
+// (350) 229 / 259, 8192x8192 -> 8192 462 / 435.
 int pick_packed_tile(const tasq_opts *o, long long M, long long N, long long K)
 {
     const int f = forced_ptile(o);
@@ -188,7 +192,7 @@ int pick_packed_tile(const tasq_opts *o, long long M, long long N, long long K)
         return f;
     const long long t256 = ((M + 255) / 256) * ((N + 255) / 256);
     const long long t128x256 = ((M + 127) / 128) * ((N + 255) / 256);
-    if (t256 >= 140 || M * N * K >= (1LL << 38))
+    if ((t256 >= 140 && t256 <= kComputeUnits) || M * N * K >= (1LL << 38))
         return tasq::PTILE_256x256_K128_W8;
     if (t128x256 >= 200)
         return tasq::PTILE_128x256_K128_W4;
@@ -202,25 +206,80 @@ int pick_packed_grouped_tile(const tasq_opts *o)
     return f >= 0 ? f : tasq::PTILE_256x256_K128_W8;
 }
 
-// Tile used for a single (non-grouped) launch, from the same sweep: 256x256
-// tiles (8 waves, BK 128) from 140 tiles up, 128x128 tiles while they give
-// 200 tiles, 64x64 tiles below that so that more workgroups cover the 256
-// compute units.
-// A conv on byte-aligned operands takes no 256x256 tiles: its chunks' taps
-// and shifts need more registers than that tile leaves (96x96 pixels 650 ->
-// 650: 93.8 us with 128x128 tiles, 152 with 256x256, 95.9 with 64x64).
-int pick_tile(const tasq_opts *o, long long M, long long N, bool any_conv = false)
+// Estimated time in us of nk K tiles (128 bytes) over output tiles of the
+// row-major GEMM kernels, fitted to a sweep of the DiT/UNet layer shapes
+// (M 1024..16384, K 320..11200; most within 10%).
+//   256x256 (persistent walk, one workgroup per compute unit): rounds of
+//     8.5 + 1.35 nk;
+//   128x128 (two workgroups per compute unit): rounds of 512 tiles of 4 +
+//     1.15 nk, which overlap from two rounds on; a last round of at most one
+//     workgroup per compute unit runs at 0.65 nk.
+double cost_256(long long tiles, long long nk)
+{
+    return (double)((tiles + kComputeUnits - 1) / kComputeUnits) * (8.5 + 1.35 * nk);
+}
+
+double cost_128(long long tiles, long long nk)
+{
+    const long long slots = 2 * kComputeUnits, full = tiles / slots, rem = tiles % slots;
+    if (full >= 2)
+        return (double)tiles / slots * (4.0 + 1.15 * nk);
+    const double last = rem == 0 ? 0.0 : rem <= kComputeUnits ? 0.65 * nk : 1.15 * nk;
+    return (full ? 4.0 + 1.15 * nk : 4.0) + last;
+}
+
+// Tile used for a single (non-grouped) launch: 64x64 tiles, so that more
+// workgroups cover the 256 compute units, while 128x128 would give fewer
+// than 200; above that the cheaper of 128x128 and the persistent 256x256
+// walk.  us, 128x128 / 256x256: 4096x640 -> 5120 (320 tiles of 256x256, a
+// second round a quarter full) 23.7 / 30.9, 2048x1280 -> 10240 (320) 34.2 /
+// 42.4, 8192x1152 -> 3456 (448) 48.9 / 46.9, 4096x2240 -> 2240 (144) 40.0 /
+// 33.8, 4096x2240 -> 11200 (704) 124.6 / 104.6.
+// Byte-aligned operands have no persistent walk: 256x256 tiles from 140 up
+// (8192x1151 -> 3456 64 us against 69), and none for a conv, whose chunks'
+// taps and shifts need more registers than that tile leaves (96x96 pixels
+// 650 -> 650: 93.8 us with 128x128 tiles, 152 with 256x256, 95.9 with 64x64).
+int pick_tile(const tasq_opts *o, long long M, long long N, long long K, bool aligned, bool conv)
 {
     const int f = forced_tile(o);
     if (f >= 0)
         return f;
     const long long t256 = ((M + 255) / 256) * ((N + 255) / 256);
     const long long t128 = ((M + 127) / 128) * ((N + 127) / 128);
-    if (t256 >= 140 && !any_conv)
+    const long long nk = (K + 127) / 128;
+    const bool big = aligned && !conv ? cost_256(t256, nk) < cost_128(t128, nk)
+                                      : t256 >= 140 && (aligned || !conv);
+    if (t128 >= 200 && big)
         return tasq::TILE_256x256_K128_W8_PF1;
     if (t128 >= 200)
         return tasq::TILE_128x128_K128_W4_PF2;
     return tasq::TILE_64x64_K128_W4_PF2;
+}
+
+// Wave groups sharing each tile's K range (kgroups.hip), for a single layer
+// whose tiles leave compute units short of waves.  us, plain / grouped:
+// 128x128 tiles, two groups: 2000x4608 -> 1152 (144 tiles) 26.5 / 22.6, 64x64
+// pixels 640 -> 640 3x3 (160) 38.6 / 32.5, 2048x2048 -> 2048 (256) 15.2 / 14.2,
+// but 4942x861 -> 640 (195, K too short) 12.5 / 12.9.  64x64 tiles, four
+// groups: 128x4608 -> 1152 (36) 14.1 / 10.7, 300x4608 -> 1152 (90) 14.2 / 11.2,
+// 18x25 pixels 640 -> 640 (80) 21.5 / 15.6; two groups: 1000x2560 -> 640 (160)
+// 9.3 / 8.1, 32x32 pixels 1280 -> 1280 (320) 57.6 / 49.0, 777x1153 -> 1111 (234)
+// 9.6 / 8.9.  Beyond those counts the groups only contend for the compute
+// unit's loads (1024x1280 -> 3840, 960 tiles of 64x64: 11.9 / 13.7).
+tasq::KGroupTile pick_kgroups(const tasq_opts *o, long long M, long long N, long long K)
+{
+    if (forced_tile(o) >= 0)
+        return tasq::KG_NONE;
+    const long long t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    const long long t64 = ((M + 63) / 64) * ((N + 63) / 64);
+    const long long nk = (K + 127) / 128;
+    if (t128 >= 130 && t128 <= kComputeUnits && nk >= 14)
+        return tasq::KG_128x128_2;
+    if (t64 <= kComputeUnits / 2 && nk >= 8)
+        return tasq::KG_64x64_4;
+    if (t64 <= kComputeUnits + kComputeUnits / 4 && nk >= 8)
+        return tasq::KG_64x64_2;
+    return tasq::KG_NONE;
 }
 
 // Split-K of single-layer calls with the row-major weight.  A layer with few
@@ -246,6 +305,18 @@ int auto_splits(long long M, long long N, long long K)
     if (s > smax)
         s = smax;
     return s >= 2 ? (int)s : 1;
+}
+
+// The ranges actually taken, at most those the workspace is sized for: enough
+// that 128x128 tiles times ranges fill the two workgroups per compute unit
+// and no more, each range's partial output being written and read again (the
+// conv above, 80 tiles of 128x128: 6 ranges 32.6 us, 4 37.5, 3 37.5, 2 47.8;
+// 256x256 tiles with 10 ranges 39.4).
+int chosen_splits(long long M, long long N, long long K)
+{
+    const long long t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    const long long s = std::max(2LL, 2LL * kComputeUnits / t128);
+    return (int)std::min<long long>(s, auto_splits(M, N, K));
 }
 
 // K range per split (a multiple of 128, the largest BK) and the resulting
@@ -288,7 +359,7 @@ constexpr size_t schedule_partials_offset(int L)
 int pick_split_tile(const tasq_opts *o)
 {
     const int f = forced_tile(o);
-    return f >= 0 ? f : tasq::TILE_256x256_K128_W8_PF1;
+    return f >= 0 ? f : tasq::TILE_128x128_K128_W4_PF2;
 }
 
 // Tile of the grouped per-step launch: 256x256, unless one 256x256 tile of
@@ -466,17 +537,21 @@ int launch_layer(const LayerDesc &d, const tasq_opts *o, hipStream_t stream,
         else
             aligned = (d.K % 16) == 0 && aligned16(d.X) && aligned16(d.W);
         aligned = aligned && fits_buffers(d);
-        // Split-K: forced (split_k >= 2, needs the workspace) or chosen
-        // (split_k == 0, only with a large enough workspace).
+            // Split-K: forced (split_k >= 2, needs the workspace) or chosen
+        // (split_k == 0, only with a workspace of tasq_workspace_bytes).
         const int req = o ? o->split_k : 0;
         int splits = 1, kchunk = 0;
         if (allow_split && req != 1 && d.K > 128) {
-            const int s = req >= 2 ? req : auto_splits(d.M, d.N, d.K);
+            const unsigned long long room = o && o->workspace ? o->workspace_bytes : 0;
+            int s = req;
+            if (req == 0) {
+                const size_t whole = tasq_workspace_bytes(d.M, d.N, d.K);
+                s = whole && room >= whole ? chosen_splits(d.M, d.N, d.K) : 1;
+            }
             if (s > 1) {
                 split_geometry(d.K, s, kchunk, splits);
                 const unsigned long long need = 4ULL * splits * (unsigned long long)d.M * d.N;
-                const bool ws_ok = o && o->workspace && o->workspace_bytes >= need &&
-                                   need < (1ULL << 31);
+                const bool ws_ok = room >= need && need < (1ULL << 31);
                 if (!ws_ok && req >= 2)
                     return TASQ_ERR_WORKSPACE;
                 if (!ws_ok || !aligned)
@@ -489,8 +564,12 @@ int launch_layer(const LayerDesc &d, const tasq_opts *o, hipStream_t stream,
             if (e == hipSuccess)
                 e = tasq::launch_split_finish(d, part, splits, stream);
         } else {
-            const bool any_conv = !aligned && d.kind == tasq::KIND_CONV3X3;
-            e = tasq::tile_ops(pick_tile(o, d.M, d.N, any_conv)).single(d, aligned, stream);
+            const tasq::KGroupTile kg = pick_kgroups(o, d.M, d.N, d.K);
+            const bool conv = d.kind == tasq::KIND_CONV3X3;
+            e = kg != tasq::KG_NONE
+                    ? tasq::launch_kgroups(d, kg, aligned, stream)
+                    : tasq::tile_ops(pick_tile(o, d.M, d.N, d.K, aligned, conv))
+                          .single(d, aligned, stream);
         }
     }
     return e == hipSuccess ? TASQ_OK : TASQ_ERR_HIP;

@@ -96,6 +96,11 @@ struct TileOps {
                                     int stage, int wgs_per_xcd, int parties, hipStream_t stream);
 };
 
+// Output tile and wave groups sharing its K range (kgroups.hip): single
+// layers with few output tiles.
+enum KGroupTile : int { KG_NONE = 0, KG_64x64_2, KG_64x64_4, KG_128x128_2 };
+hipError_t launch_kgroups(const LayerDesc &d, KGroupTile tile, bool aligned, hipStream_t stream);
+
 // Sums split-K partials and applies the dequantisation epilogue (splitk.hip).
 hipError_t launch_split_finish(const LayerDesc &d, const int32_t *part, int splits,
                                hipStream_t stream);
