@@ -173,35 +173,68 @@ struct OneLayer {
     __device__ __forceinline__ int bits(int) const { return d.bits; }
 };
 
-// One workgroup per compute unit walks its XCD's run of work units (as in
-// k_masked_gemm_persistent).  g counts K tiles across the walk: K tile t of
+// The work units that a workgroup walks: every wgs-th of its part of its XCD's
+// run (as in k_masked_gemm_persistent), ...
+struct RunWalk {
+    int u, uend, wgs;
+
+    __device__ __forceinline__ RunWalk(const XcdRuns &runs, int parties)
+    {
+        constexpr int NX = 8;
+        wgs = gridDim.x / NX / parties;
+        const int x = blockIdx.x % NX, j = blockIdx.x / NX;
+        const int part = j % parties;
+        const int xbeg = runs.begin[x], xend = runs.begin[x + 1];
+        const int pspan = (xend - xbeg + parties - 1) / parties;
+        const int ubeg = xbeg + part * pspan;
+        uend = min(xend, ubeg + pspan);
+        u = ubeg + j / parties;
+    }
+    __device__ __forceinline__ bool live() const { return u < uend; }
+    __device__ __forceinline__ void next() { u += wgs; }
+};
+
+// ... or a list of its own: row r of `order` holds every workgroup's r-th
+// unit, kNoUnit after its last.  Read as aligned dwords (see table_bits).
+struct ListWalk {
+    const uint32_t *__restrict__ order;
+    int p, u;
+
+    __device__ __forceinline__ ListWalk(const uint16_t *o)
+        : order(reinterpret_cast<const uint32_t *>(o)), p(blockIdx.x)
+    {
+        load();
+    }
+    __device__ __forceinline__ void load()
+    {
+        u = (int)((order[p >> 1] >> (16 * (p & 1))) & 0xffffu);
+    }
+    __device__ __forceinline__ bool live() const { return u != kNoUnit; }
+    __device__ __forceinline__ void next()
+    {
+        p += gridDim.x;
+        load();
+    }
+};
+
+// One workgroup per compute unit walks its work units.  g counts K tiles across the walk: K tile t of
 // the current tile is global K tile g0 + t, in activation stage (g0+t) % 3
 // and weight stage (g0+t) % 2; weight K tile t sits in register slot t % 2
 // from its load until its LDS store (both slots are empty at a tile
 // boundary, so the slots need not rotate across tiles).
-template <class C, bool EXTRAS, class Layers>
-__device__ __forceinline__ void persistent_ds(const Layers &layers, const XcdRuns &runs,
-                                              int parties, char *sm)
+template <class C, bool EXTRAS, class Layers, class Walk>
+__device__ __forceinline__ void persistent_ds(const Layers &layers, Walk walk, char *sm)
 {
     using Ops = PersOperands<C>;
     char *const smA = sm;
     char *const smB = sm + pers::kAStages * Ops::A_STAGE;
-    constexpr int NX = 8;
     constexpr int KK = Ops::KK, WRITE_KK = Ops::WRITE_KK;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
 
-    const int wgs = gridDim.x / NX / parties;
-    const int x = blockIdx.x % NX, j = blockIdx.x / NX;
-    const int part = j % parties, jj = j / parties;
-    const int xbeg = runs.begin[x], xend = runs.begin[x + 1];
-    const int pspan = (xend - xbeg + parties - 1) / parties;
-    const int ubeg = xbeg + part * pspan;
-    const int uend = min(xend, ubeg + pspan);
-    int u = ubeg + jj;
-    if (u >= uend)
+    if (!walk.live())
         return;
 
     auto a_stage = [&](int g) { return smA + (g % pers::kAStages) * Ops::A_STAGE; };
@@ -223,9 +256,9 @@ __device__ __forceinline__ void persistent_ds(const Layers &layers, const XcdRun
         ops.load_b(ring[1], t0 + 1);
     };
 
-    int seg = layers.find(u);
+    int seg = layers.find(walk.u);
     int m0, n0;
-    unit_coords<C>(layers.desc(seg), u, m0, n0);
+    unit_coords<C>(layers.desc(seg), walk.u, m0, n0);
     int bits = layers.bits(seg);
     int g0 = 0;                       // global K tile of the current tile's K tile 0
     bool first = true;
@@ -351,11 +384,11 @@ __device__ __forceinline__ void persistent_ds(const Layers &layers, const XcdRun
         const LayerDesc &dc = d;
         const int mc = m0, nc = n0;
         const int g1 = g0 + nk;
-        u += wgs;
-        const bool more = u < uend;
+        walk.next();
+        const bool more = walk.live();
         if (more) {
-            seg = layers.find(u);
-            unit_coords<C>(layers.desc(seg), u, m0, n0);
+            seg = layers.find(walk.u);
+            unit_coords<C>(layers.desc(seg), walk.u, m0, n0);
             bits = layers.bits(seg);
             int t2 = tid;
             asm volatile("" : "+v"(t2));
@@ -418,7 +451,18 @@ k_masked_gemm_persistent_ds(const LayerDesc *__restrict__ descs, int L, int tota
                             const uint8_t *__restrict__ table, int S, int stage, int parties)
 {
     __shared__ __attribute__((aligned(1024))) char sm[PersOperands<C>::LDS];
-    persistent_ds<C, EXTRAS>(StepLayers{descs, table, L, S, stage}, runs, parties, sm);
+    persistent_ds<C, EXTRAS>(StepLayers{descs, table, L, S, stage}, RunWalk(runs, parties), sm);
+}
+
+// The step as lists of units (unit_lists in tasq_api.cpp).
+template <class C, bool EXTRAS>
+__global__ void __launch_bounds__(C::NT, C::OCC)
+k_masked_gemm_lists_ds(const LayerDesc *__restrict__ descs, int L,
+                       const uint16_t *__restrict__ order, const uint8_t *__restrict__ table,
+                       int S, int stage)
+{
+    __shared__ __attribute__((aligned(1024))) char sm[PersOperands<C>::LDS];
+    persistent_ds<C, EXTRAS>(StepLayers{descs, table, L, S, stage}, ListWalk(order), sm);
 }
 
 // A single layer of at least about half a tile per compute unit, whose K loop
@@ -432,7 +476,7 @@ __global__ void __launch_bounds__(C::NT, C::OCC) k_masked_gemm_ds(LayerDesc d, X
     __shared__ __attribute__((aligned(1024))) char sm[PersOperands<C>::LDS];
     if constexpr (!EXTRAS)          // with them the scalar registers would not hold it all
         pin(d);
-    persistent_ds<C, EXTRAS>(OneLayer{d}, runs, 1, sm);
+    persistent_ds<C, EXTRAS>(OneLayer{d}, RunWalk(runs, 1), sm);
 }
 
 template <class C, bool EXTRAS>
@@ -446,6 +490,16 @@ hipError_t launch_persistent_ds_cfg(const LayerDesc *d_descs, int L, int total_t
     dim3 g((unsigned)(8 * wgs_per_xcd)), b(C::NT);
     hipLaunchKernelGGL((k_masked_gemm_persistent_ds<C, EXTRAS>), g, b, 0, stream, d_descs, L,
                        total_tiles, runs, d_table, S, stage, parties);
+    return hipGetLastError();
+}
+
+template <class C, bool EXTRAS>
+hipError_t launch_lists_ds_cfg(const LayerDesc *d_descs, int L, const uint16_t *d_order,
+                               const uint8_t *d_table, int S, int stage, hipStream_t stream)
+{
+    dim3 g(kListWorkgroups), b(C::NT);
+    hipLaunchKernelGGL((k_masked_gemm_lists_ds<C, EXTRAS>), g, b, 0, stream, d_descs, L, d_order,
+                       d_table, S, stage);
     return hipGetLastError();
 }
 
@@ -480,7 +534,9 @@ hipError_t launch_single_ds(const LayerDesc &din, bool aligned, hipStream_t stre
                                     &launch_planes_cfg<CFG>, &launch_grouped_cfg<CFG>,      \
                                     &launch_split_cfg<CFG>,                                 \
                                     &launch_persistent_ds_cfg<CFG, false>,                  \
-                                    &launch_persistent_ds_cfg<CFG, true>};                  \
+                                    &launch_persistent_ds_cfg<CFG, true>,                   \
+                                    &launch_lists_ds_cfg<CFG, false>,                       \
+                                    &launch_lists_ds_cfg<CFG, true>};                  \
         return ops;                                                                         \
     }
 

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -32,6 +33,19 @@ constexpr double kImbalanceLimit = 1.10;
 // 128 each on average) spends about 0.66 ms in tile ends, 4.5 us per tile,
 // against 1.9 us per K tile: about 300 bytes of K.
 constexpr double kTileFixedK = 384.0;
+
+// Persistent steps of up to this many tiles run over lists of units, which the
+// host deals out on each call, where these cut the busiest workgroup's cost by
+// a tenth.  us per step, runs / lists: 1 PixArt block at 4096 tokens (672
+// tiles) 107 / 83, 6 at 700 (756) 109.5 / 97.6, 1 SANA block at 3000 (1068)
+// 197.8 / 179.4, 2 PixArt blocks at 4096 (1344) 165.2 / 157.3; but 6 at 2048
+// (2016) 225.3 / 231.1: six tiles per workgroup and more even out, and layers
+// in turn keep the stores of shallow tiles under the matrix work of deep ones.
+constexpr long long kListMaxUnits = 1536;
+constexpr double kListGain = 0.9;
+constexpr long long kStepCostMaxTiles = 4096;   // pick_step_tile
+// A tile of theirs takes about 8.5 us plus 1.6 per K tile of 128 bytes.
+constexpr double kListFixedK = 680.0;
 
 // The XCD runs of a persistent launch: contiguous in the work-unit order
 // (neighbouring tiles share operands in one L2) and cut at about equal cost,
@@ -66,6 +80,78 @@ tasq::XcdRuns cost_runs(const std::vector<LayerDesc> &segs, long long total)
     return r;
 }
 
+// Cost of the busiest workgroup of a persistent launch over `runs`.
+double runs_makespan(const std::vector<LayerDesc> &segs, const tasq::XcdRuns &runs)
+{
+    double load[tasq::kListWorkgroups] = {0}, mx = 0;
+    constexpr int wgs = tasq::kListWorkgroups / kXcds;
+    size_t l = 0;
+    for (int x = 0; x < kXcds; ++x)
+        for (int u = runs.begin[x]; u < runs.begin[x + 1]; ++u) {
+            while (l + 1 < segs.size() && segs[l + 1].tile_begin <= u)
+                ++l;
+            double &w = load[x * wgs + (u - runs.begin[x]) % wgs];
+                w += segs[l].K + kListFixedK;
+            mx = w > mx ? w : mx;
+        }
+    return mx;
+}
+
+// Work units of a persistent step as one list per workgroup (ListWalk): the
+// layers from the deepest K down, each cut into one contiguous run of tiles
+// per XCD (tiles that share operands meet in one L2), and within an XCD each
+// next tile to the workgroup with the least work so far.  A step of few tiles
+// per workgroup whose layers differ in K ends when the workgroup that drew a
+// deep tile late is done: the busiest over the UNet block's linear layers (804
+// tiles of 256x256, K 640..5120) has 1.42 times the mean work in layer order
+// and 1.09 times with lists.
+// Returns the cost of the busiest workgroup.
+double unit_lists(const std::vector<LayerDesc> &segs, std::vector<uint16_t> &order)
+{
+    constexpr int wgs = tasq::kListWorkgroups / kXcds;
+    std::vector<const LayerDesc *> by_k;
+    for (const LayerDesc &d : segs)
+        by_k.push_back(&d);
+    std::stable_sort(by_k.begin(), by_k.end(),
+                     [](const LayerDesc *a, const LayerDesc *b) { return a->K > b->K; });
+    double load[tasq::kListWorkgroups] = {0}, xload[kXcds] = {0}, mx = 0;
+    std::vector<uint16_t> list[tasq::kListWorkgroups];
+    size_t rows = 0;
+    for (const LayerDesc *d : by_k) {
+        const int n = d->tiles_m * d->tiles_n;
+        const double cost = d->K + kListFixedK;
+        // An eighth of the layer per XCD, the odd tiles to those with the
+        // least work so far.
+        int take[kXcds];
+        for (int x = 0; x < kXcds; ++x) {
+            take[x] = n / kXcds;
+            xload[x] += take[x] * cost;
+        }
+        for (int i = 0; i < n % kXcds; ++i) {
+            const int x = (int)(std::min_element(xload, xload + kXcds) - xload);
+            ++take[x];
+            xload[x] += cost;
+        }
+        int u = d->tile_begin;
+        for (int x = 0; x < kXcds; ++x)
+            for (int i = 0; i < take[x]; ++i, ++u) {
+                double *const w = load + x * wgs;
+                const int j = (int)(std::min_element(w, w + wgs) - w);
+                w[j] += cost;
+                mx = w[j] > mx ? w[j] : mx;
+                // workgroup j of XCD x is block 8 j + x
+                std::vector<uint16_t> &li = list[j * kXcds + x];
+                li.push_back((uint16_t)u);
+                rows = li.size() > rows ? li.size() : rows;
+            }
+    }
+    order.assign((rows + 1) * tasq::kListWorkgroups, (uint16_t)tasq::kNoUnit);
+    for (int w = 0; w < tasq::kListWorkgroups; ++w)
+        for (size_t r = 0; r < list[w].size(); ++r)
+            order[r * tasq::kListWorkgroups + w] = list[w][r];
+    return mx;
+}
+
 // Heaviest XCD run over the mean, for the per-layer tile order, a tile
 // costing about its K plus a fixed part for loading and writing the tile.
 double xcd_imbalance(const std::vector<LayerDesc> &descs, long long G)
@@ -98,6 +184,14 @@ double xcd_imbalance(const std::vector<LayerDesc> &descs, long long G)
     for (double w : work)
         mx = w > mx ? w : mx;
     return total > 0 ? mx / (total / kXcds) : 1.0;
+}
+
+long long grouped_tiles(const std::vector<LayerDesc> &descs, const tasq::TileShape &ts)
+{
+    long long n = 0;
+    for (const LayerDesc &d : descs)
+        n += (long long)((d.M + ts.bm - 1) / ts.bm) * ((d.N + ts.bn - 1) / ts.bn);
+    return n;
 }
 
 constexpr size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -152,8 +246,9 @@ int check_tuning(const tasq_opts *o)
 
 // The grouped step over linear layers without low-rank or weight-zero-point
 // terms runs as a persistent launch (one workgroup per compute unit, tile
-// boundaries overlapped) with the 256x256 tile once there are at least two
-// tiles per compute unit, unless the caller forces it off or on.
+// boundaries overlapped) with the 256x256 tile where pick_step_tile's estimate
+// says so, otherwise once there are at least two tiles per compute unit, unless
+// the caller forces it off or on.
 bool use_persistent(const tasq_opts *o, bool big_tile, long long total)
 {
     if (o && o->persistent)
@@ -362,25 +457,60 @@ int pick_split_tile(const tasq_opts *o)
     return f >= 0 ? f : tasq::TILE_128x128_K128_W4_PF2;
 }
 
-// Tile of the grouped per-step launch: 256x256, unless one 256x256 tile of
-// the longest-K layer costs more than a compute unit's even share of the
-// whole step; then that tile alone sets the step time (the 3x3 conv of the
-// SDXL-Turbo block: K = 11520 against 0.5 GOP per CU), and 128x128 tiles cut
-// it by four (measured 0.230 -> 0.178 ms per step there, no change on the
-// DiT blocks, which keep 256x256).
-int pick_grouped_tile(const tasq_opts *o, const std::vector<LayerDesc> &descs)
+// Tiles of the grouped per-step launch.
+enum StepTile { STEP_256, STEP_128, STEP_64, STEP_64_2 };
+
+// The tiles of the grouped step over linear layers, by an estimate in us of
+// each form's time: the longest tile on its own, or all tiles' work spread
+// over the chip and a share of the longest one for the uneven end.  nk is a
+// layer's K tiles of 128 bytes; the constants are fitted to 45 steps of 1 to
+// 20 blocks of the DiT shapes at 65 to 4096 tokens (most within 15%).
+//   256x256 (persistent, lists): tiles of 8.5 + 1.6 nk, 256 at a time;
+//   128x128: 4 + 1.15 nk, 512 at a time;
+//   64x64: 1050 K tiles per us, each tile costing nk + 1;
+//   64x64 with K shared by two wave groups: 28% less of them, half the chain.
+// us per step, 256 / 128 / 64 / 64 in two groups:
+//   1 PixArt block, 100 tokens 45 / 25.5 / 17.5 / 14.0
+//   1 PixArt block, 700 tokens 48.5 / 32.0 / 25.9 / 32.3
+//   2 PixArt blocks, 700 tokens 55.2 / 41.5 / 47.2 / 57.4
+//   1 PixArt block, 2048 tokens 59 / 50 / 63 / 78
+//   UNet block (conv apart) 79 / 82 / 115 / 136
+//   1 SANA block, 1024 tokens 72 / 87 / 120 / 129
+//   6 PixArt blocks, 1024 tokens 127 / 141 / 188 / 227
+// The former rule, 256x256 unless one tile outweighed a compute unit's share
+// of the step and 128x128 then, took 28 us on the first, 62 on the fourth, 99
+// on the fifth and 91.6 on the sixth.
+// Many tiles per compute unit leave no uneven end, and steps with a conv
+// (which has no persistent form), forced tiles or a forced form keep to the
+// former rule.
+StepTile pick_step_tile(const tasq_opts *o, const std::vector<LayerDesc> &descs, bool any_conv)
 {
-    const int f = forced_tile(o);
-    if (f >= 0)
-        return f;
-    double total = 0, longest = 0;
+    double total = 0, longest = 0, t256 = 0;
     for (const LayerDesc &d : descs) {
         total += 2.0 * d.M * (double)d.N * d.K;
-        const double tile = 2.0 * 256 * 256 * (double)d.K;
-        longest = tile > longest ? tile : longest;
+        longest = std::max(longest, (double)d.K);
+        t256 += (double)((d.M + 255) / 256) * ((d.N + 255) / 256);
     }
-    return longest > total / kComputeUnits ? tasq::TILE_128x128_K128_W4_PF2
-                                           : tasq::TILE_256x256_K128_W8_PF1;
+    if (any_conv || (o && o->persistent) || t256 > kStepCostMaxTiles)
+        return 2.0 * 256 * 256 * longest > total / kComputeUnits ? STEP_128 : STEP_256;
+    double w256 = 0, w128 = 0, w64 = 0;
+    for (const LayerDesc &d : descs) {
+        const double nk = (d.K + 127) / 128;
+        auto tiles = [&](int b) {
+            return (double)((d.M + b - 1) / b) * ((d.N + b - 1) / b);
+        };
+        w256 += tiles(256) * (8.5 + 1.6 * nk) / kComputeUnits;
+        w128 += tiles(128) * (4.0 + 1.15 * nk) / (2 * kComputeUnits);
+        w64 += tiles(64) * (1.0 + nk) / 1050.0;
+    }
+    const double nk = std::ceil(longest / 128);
+    const double a256 = 6.0 + 1.15 * nk, a128 = 4.0 + 0.65 * nk;
+    const double a64 = 3.0 + 0.48 * nk, a64_2 = 3.0 + 0.28 * nk;
+    w256 *= 1.12;
+    const double cost[] = {std::max(a256, w256) + 0.35 * std::min(a256, w256),
+                           std::max(a128, w128 + 0.55 * a128), std::max(a64, w64 + 0.3 * a64),
+                           std::max(a64_2, 1.28 * w64 + 0.3 * a64_2)};
+    return (StepTile)(std::min_element(cost, cost + 4) - cost);
 }
 
 bool use_bitplane(const tasq_opts *o) { return o && o->variant == TASQ_VARIANT_BITPLANE; }
@@ -537,7 +667,7 @@ int launch_layer(const LayerDesc &d, const tasq_opts *o, hipStream_t stream,
         else
             aligned = (d.K % 16) == 0 && aligned16(d.X) && aligned16(d.W);
         aligned = aligned && fits_buffers(d);
-            // Split-K: forced (split_k >= 2, needs the workspace) or chosen
+        // Split-K: forced (split_k >= 2, needs the workspace) or chosen
         // (split_k == 0, only with a workspace of tasq_workspace_bytes).
         const int req = o ? o->split_k : 0;
         int splits = 1, kchunk = 0;
@@ -1309,6 +1439,9 @@ static int run_schedule_impl(const tasq_layer *layers, int L, const uint8_t *b_t
         hipError_t (*launch_persistent)(const LayerDesc *, int, int, const tasq::XcdRuns &,
                                         const uint8_t *, int, int, int, int,
                                         hipStream_t) = nullptr;
+        hipError_t (*launch_lists)(const LayerDesc *, int, const uint16_t *, const uint8_t *, int,
+                                   int, hipStream_t) = nullptr;
+        bool persistent_pays = false;     // chosen as a persistent launch by cost
         bool big_tile = false;      // the 256x256 tile, which AUTO runs persistent
         bool extras = false;
         for (int l = 0; l < LG; ++l)
@@ -1325,14 +1458,33 @@ static int run_schedule_impl(const tasq_layer *layers, int L, const uint8_t *b_t
                 launch_persistent = ops.persistent;
             big_tile = ptile == tasq::PTILE_256x256_K128_W8;
         } else {
-            const int tile = pick_grouped_tile(opts, descs);
+            const int f = forced_tile(opts);
+            const StepTile step = f >= 0 ? STEP_256 : pick_step_tile(opts, descs, any_conv);
+            constexpr int tile_of[] = {tasq::TILE_256x256_K128_W8_PF1,
+                                       tasq::TILE_128x128_K128_W4_PF2,
+                                       tasq::TILE_64x64_K128_W4_PF2,
+                                       tasq::TILE_64x64_K128_W4_PF2};
+            const int tile = f >= 0 ? f : tile_of[step];
             const tasq::TileOps &ops = tasq::tile_ops(tile);
             ts = ops.shape;
-            launch_step = ops.grouped;
-            if (!any_conv)
+            launch_step = step == STEP_64_2 ? tasq::launch_kgroups_2x64 : ops.grouped;
+            if (!any_conv) {
                 launch_persistent = extras ? ops.persistent_extras : ops.persistent;
+                launch_lists = extras ? ops.lists_extras : ops.lists;
+            }
             big_tile = tile == tasq::TILE_256x256_K128_W8_PF1;
+            persistent_pays = f < 0 && !any_conv && step == STEP_256 && !(opts && opts->persistent);
         }
+        // The one-workgroup-per-tile launches run the deepest layers first too,
+        // so that no deep tile starts when the others are done (us per step of
+        // one block in 128x128 tiles, layer order / by K: 1024 tokens 41.9 /
+        // 35.1, 2048 64.7 / 49.9).
+        const bool persistent_step =
+            launch_persistent && (persistent_pays ||
+                                  use_persistent(opts, big_tile, grouped_tiles(descs, ts)));
+        if (!all_skinny && !persistent_step)
+            std::stable_sort(descs.begin(), descs.end(),
+                             [](const LayerDesc &x, const LayerDesc &y) { return x.K > y.K; });
         long long total = 0;
         for (int l = 0; l < LG; ++l) {
             LayerDesc &d = descs[l];
@@ -1346,7 +1498,7 @@ static int run_schedule_impl(const tasq_layer *layers, int L, const uint8_t *b_t
         }
         if (total == 0 && solo.empty())
             return TASQ_OK;
-        if (!use_persistent(opts, big_tile, total))
+        if (!persistent_step)
             launch_persistent = nullptr;
         const int wgs_per_xcd = persistent_wgs_per_xcd(opts);
         const int parties = persistent_parties(opts, wgs_per_xcd);
@@ -1362,13 +1514,20 @@ static int run_schedule_impl(const tasq_layer *layers, int L, const uint8_t *b_t
         if (!all_skinny && !launch_persistent &&
             xcd_imbalance(descs, total) > kImbalanceLimit) {
             segs.reserve((size_t)LG * kXcds);
+            // Unit p of the layer order counts towards run p % kXcds, so that
+            // the rounds have the very sizes of the XCDs' runs (xcd_remap)
+            // and no run ends with the next round's first tiles.
+            auto before = [](long long p, int r) { return (p + kXcds - 1 - r) / kXcds; };
+            std::vector<long long> next(LG, 0);
             long long begin = 0;
             for (int r = 0; r < kXcds; ++r)
                 for (int l = 0; l < LG; ++l) {
+                    const long long p = descs[l].tile_begin;
                     const long long n = (long long)descs[l].tiles_m * descs[l].tiles_n;
-                    const long long lo = n * r / kXcds, hi = n * (r + 1) / kXcds;
+                    const long long lo = next[l], hi = lo + before(p + n, r) - before(p, r);
                     if (hi <= lo)
                         continue;
+                    next[l] = hi;
                     LayerDesc d = descs[l];
                     d.tile_first = (int)lo;
                     d.tile_begin = (int)begin;
@@ -1380,13 +1539,33 @@ static int run_schedule_impl(const tasq_layer *layers, int L, const uint8_t *b_t
         }
         const int nseg = (int)segs.size();
         const tasq::XcdRuns runs = cost_runs(segs, total);
-        // The segments, then the table, in one block of the workspace.
+        // The persistent step over lists of units where they spare the
+        // busiest workgroup enough of its work, and where they fit the part
+        // of the layer list's room that a persistent launch leaves unused
+        // (one descriptor of kXcds per layer).
         const size_t desc_bytes = (size_t)nseg * sizeof(LayerDesc);
-        std::vector<uint8_t> block(round_up(desc_bytes + (size_t)L * S, 16), 0);
+        const size_t order_at = round_up(desc_bytes + (size_t)L * S, 16);
+        std::vector<uint16_t> order;
+        if (!launch_persistent || total > kListMaxUnits ||
+            (opts && (opts->persistent_wgs || opts->persistent_parties)))
+            launch_lists = nullptr;
+        if (launch_lists) {
+            if (unit_lists(segs, order) > kListGain * runs_makespan(segs, runs) ||
+                order_at + 2 * order.size() > schedule_partials_offset(L)) {
+                order.clear();
+                launch_lists = nullptr;
+            }
+        }
+        // The segments, the table, then the lists, in one block of the
+        // workspace.
+        std::vector<uint8_t> block(order_at + round_up(2 * order.size(), 16), 0);
         std::memcpy(block.data(), segs.data(), desc_bytes);
         std::memcpy(block.data() + desc_bytes, b_table, (size_t)L * S);
+        if (!order.empty())
+            std::memcpy(block.data() + order_at, order.data(), 2 * order.size());
         LayerDesc *d_descs = reinterpret_cast<LayerDesc *>(ws);
         uint8_t *d_table = reinterpret_cast<uint8_t *>(ws) + desc_bytes;
+        const uint16_t *d_order = reinterpret_cast<uint16_t *>(ws + order_at);
         if (upload(ws, block.data(), block.size(), st) != hipSuccess)
             return TASQ_ERR_HIP;
         // Schedules ignore split_k: a layer launched on its own takes the
@@ -1414,6 +1593,7 @@ static int run_schedule_impl(const tasq_layer *layers, int L, const uint8_t *b_t
             const hipError_t e =
                 all_skinny ? tasq::launch_skinny_grouped(d_descs, nseg, (int)total, max_m, src,
                                                          d_table, S, s, st)
+                : launch_lists ? launch_lists(d_descs, nseg, d_order, d_table, S, s, st)
                 : launch_persistent
                     ? launch_persistent(d_descs, nseg, (int)total, runs, d_table, S, s,
                                         wgs_per_xcd, parties, st)

@@ -59,6 +59,11 @@ struct XcdRuns {
     int begin[9];
 };
 
+// Unit lists of a persistent launch: one list per workgroup, kNoUnit after
+// the last unit of each.
+constexpr int kListWorkgroups = 256;
+constexpr int kNoUnit = 0xffff;
+
 // begin[0] = 0, begin[8] = total and non-decreasing in between.
 inline bool xcd_runs_valid(const XcdRuns &r, int total)
 {
@@ -94,12 +99,24 @@ struct TileOps {
     hipError_t (*persistent_extras)(const LayerDesc *d_descs, int L, int total_tiles,
                                     const XcdRuns &runs, const uint8_t *d_table, int S,
                                     int stage, int wgs_per_xcd, int parties, hipStream_t stream);
+    // The persistent step over lists of work units, kListWorkgroups
+    // workgroups (d_order: rows of kListWorkgroups units, 4-byte aligned),
+    // without and with those terms, or null.
+    hipError_t (*lists)(const LayerDesc *d_descs, int L, const uint16_t *d_order,
+                        const uint8_t *d_table, int S, int stage, hipStream_t stream);
+    hipError_t (*lists_extras)(const LayerDesc *d_descs, int L, const uint16_t *d_order,
+                               const uint8_t *d_table, int S, int stage, hipStream_t stream);
 };
 
 // Output tile and wave groups sharing its K range (kgroups.hip): single
 // layers with few output tiles.
 enum KGroupTile : int { KG_NONE = 0, KG_64x64_2, KG_64x64_4, KG_128x128_2 };
 hipError_t launch_kgroups(const LayerDesc &d, KGroupTile tile, bool aligned, hipStream_t stream);
+// 64x64 tiles with two groups over every layer of a step (TileOps::grouped;
+// linear layers only).
+hipError_t launch_kgroups_2x64(const LayerDesc *d_descs, int L, int total_tiles,
+                               const uint8_t *d_table, int S, int stage, bool any_conv,
+                               hipStream_t stream);
 
 // Sums split-K partials and applies the dequantisation epilogue (splitk.hip).
 hipError_t launch_split_finish(const LayerDesc &d, const int32_t *part, int splits,
