@@ -17,6 +17,7 @@
 // then a pass in which every workgroup folds those partials and writes its
 // share of the codes.  No atomics and no buffer to clear beforehand.  The
 // batched form runs the passes of many tensors in few launches.
+#include <type_traits>
 #include <vector>
 
 #include "quant.h"
@@ -229,15 +230,22 @@ __global__ void __launch_bounds__(256) k_act_batch(const ActLaunch L)
 //
 // T = x~ D^T for the 16-bit low-rank branch: x~ is x rounded to bfloat16
 // (nearest, ties to even), D [r x K] bfloat16, T fp32 [M x r], r <= 32.
-// One workgroup per 32-row block (grid-stride over blocks); its 8 waves take
-// interleaved 16-wide K steps, each a v_mfma_f32_32x32x16_bf16 with lane l
-// feeding row l%32 of x and column l%32 of D^T (columns past r are zero).
+// One workgroup per block of 16 or 32 rows (grid-stride over blocks); its 16
+// waves take interleaved 32-wide K steps, each a v_mfma_f32_16x16x32_bf16 per
+// 16 rows and 16 columns of D^T, with lane l feeding row l%16 of x and column
+// l%16 of D^T (columns past r are zero), 8 elements from 8*(l/16).
 // The waves' partial blocks are summed through LDS in a fixed order, so T
 // does not depend on timing.  The same pass can fold the range of x (one
 // partial per workgroup, as k_act_range), so that quantizing the codes and
-// projecting share one read of x.
+// projecting share one read of x.  Bound by the loads in flight per compute
+// unit, D's from L2 counting as much as x's: blocks of 16 rows up to one
+// workgroup per compute unit (32-row blocks left half the chip idle at 4096
+// rows), of 32 beyond, which read D half as often (8192x2240, rank 32: 15.0 us,
+// 19.0 with 16-row blocks).  Whole 128-byte lines of a row either way.  us,
+// one 32x32x16 product per block and step / now, rank 32: 4096x2240 15.1 /
+// 10.4, 300x4608 26.2 / 18.1, 16384x4608 77.1 / 58.1.
 
-typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
@@ -261,96 +269,131 @@ __device__ __forceinline__ void fold_range(float4 v, float &mn, float &mx)
     mx = fmaxf(fmaxf(mx, v.x), fmaxf(v.y, fmaxf(v.z, v.w)));
 }
 
+// NF, NB: 16-wide column and row fragments of a block.
 // FAST: K % 8 == 0 and x, D 16-byte aligned, so an in-range K step covers
-// all 8 elements of a lane; each wave then issues the loads of 4 of its K
-// steps before their MFMAs (enough bytes in flight with one workgroup per
+// all 8 elements of a lane; each wave then issues the loads of 4 of its row
+// fragments' K steps before their MFMAs (enough bytes in flight with one workgroup per
 // CU).  Otherwise every element is loaded on its own with bounds checks.
-template <bool RANGE, bool FAST>
+template <bool RANGE, bool FAST, int NF, int NB>
 __global__ void __launch_bounds__(64 * kDownWaves)
 k_lowrank_down(const float *__restrict__ x, int M, int K, const uint16_t *__restrict__ D, int r,
                float *__restrict__ T, uint32_t *__restrict__ part)
 {
-    __shared__ float red[kDownWaves][16][64];
+    __shared__ float red[kDownWaves][NB * NF * 4][64];
     __shared__ uint32_t smin[kDownWaves], smax[kDownWaves];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int half = lane >> 5;
-    const int j = lane & 31;                         // column of D^T this lane feeds
-    const int nsteps = (K + 15) / 16;
-    const int nblocks = (M + 31) / 32;
+    const int j = lane & 15, quarter = lane >> 4;
+    const int nsteps = (K + 31) / 32;
+    const int nblocks = (M + 16 * NB - 1) / (16 * NB);
     float mn = __builtin_huge_valf(), mx = -__builtin_huge_valf();
 
     for (int rb = blockIdx.x; rb < nblocks; rb += gridDim.x) {
-        const int row = rb * 32 + j;
-        const bool rok = row < M;
-        const float *xr = x + (size_t)(rok ? row : 0) * (size_t)K;
-        const uint16_t *dr = D + (size_t)(j < r ? j : 0) * (size_t)K;
-        v16f acc = {};
+        const float *xr[NB];        // the rows of x and of D (columns of D^T)
+        const uint16_t *dr[NF];     // that this lane feeds
+        bool rok[NB], dok[NF];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int row = (rb * NB + i) * 16 + j;
+            rok[i] = row < M;
+            xr[i] = x + (size_t)(rok[i] ? row : 0) * (size_t)K;
+        }
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            dok[f] = 16 * f + j < r;
+            dr[f] = D + (size_t)(dok[f] ? 16 * f + j : 0) * (size_t)K;
+        }
+        v4f acc[NB][NF] = {};
+        auto step = [&](v4u aw, v4u bw, v4f &c) {
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, aw),
+                                                        __builtin_bit_cast(v8bf, bw), c, 0, 0, 0);
+        };
         if constexpr (FAST) {
-            constexpr int U = 4;
+            constexpr int U = 4 / NB;
             for (int s0 = wave; s0 < nsteps; s0 += U * kDownWaves) {
-                float4 lo[U], hi[U];
-                v4u bw[U];
-                bool ok[U];
+                float4 lo[U][NB], hi[U][NB];
+                v4u bw[U][NF];
+                bool kin[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const int k = 16 * (s0 + u * kDownWaves) + 8 * half;
-                    const bool kin = k < K;
-                    ok[u] = rok && kin;
-                    lo[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    hi[u] = lo[u];
-                    if (ok[u]) {
-                        const float4 *p = reinterpret_cast<const float4 *>(xr + k);
-                        lo[u] = p[0];
-                        hi[u] = p[1];
+                    const int k = 32 * (s0 + u * kDownWaves) + 8 * quarter;
+                    kin[u] = k < K;
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) {
+                        lo[u][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+                        hi[u][i] = lo[u][i];
+                        if (rok[i] && kin[u]) {
+                            const float4 *p = reinterpret_cast<const float4 *>(xr[i] + k);
+                            lo[u][i] = p[0];
+                            hi[u][i] = p[1];
+                        }
                     }
-                    bw[u] = v4u{0, 0, 0, 0};
-                    if (j < r && kin)
-                        bw[u] = *reinterpret_cast<const v4u *>(dr + k);
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        bw[u][f] = v4u{0, 0, 0, 0};
+                        if (dok[f] && kin[u])
+                            bw[u][f] = *reinterpret_cast<const v4u *>(dr[f] + k);
+                    }
                 }
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (RANGE && ok[u]) {
-                        fold_range(lo[u], mn, mx);
-                        fold_range(hi[u], mn, mx);
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) {
+                        if (RANGE && rok[i] && kin[u]) {
+                            fold_range(lo[u][i], mn, mx);
+                            fold_range(hi[u][i], mn, mx);
+                        }
+                        const v4u aw = pack_bf16(lo[u][i], hi[u][i]);
+#pragma unroll
+                        for (int f = 0; f < NF; ++f)
+                            step(aw, bw[u][f], acc[i][f]);
                     }
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(v8bf, pack_bf16(lo[u], hi[u])),
-                        __builtin_bit_cast(v8bf, bw[u]), acc, 0, 0, 0);
-                }
             }
         } else {
             for (int s = wave; s < nsteps; s += kDownWaves) {
-                const int k = 16 * s + 8 * half;
-                float xv[8];
-                uint32_t dv[8];
+                const int k = 32 * s + 8 * quarter;
+                v4u bw[NF];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const bool ok = k + e < K;
-                    xv[e] = (rok && ok) ? xr[k + e] : 0.f;
-                    if (rok && ok) {
-                        mn = fminf(mn, xv[e]);
-                        mx = fmaxf(mx, xv[e]);
-                    }
-                    dv[e] = (j < r && ok) ? (uint32_t)dr[k + e] : 0u;
+                for (int f = 0; f < NF; ++f) {
+                    uint32_t dv[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        dv[e] = dok[f] && k + e < K ? (uint32_t)dr[f][k + e] : 0u;
+                    bw[f] = v4u{dv[0] | (dv[1] << 16), dv[2] | (dv[3] << 16),
+                                dv[4] | (dv[5] << 16), dv[6] | (dv[7] << 16)};
                 }
-                const v4u bw = v4u{dv[0] | (dv[1] << 16), dv[2] | (dv[3] << 16),
-                                   dv[4] | (dv[5] << 16), dv[6] | (dv[7] << 16)};
-                const v4u aw = pack_bf16(make_float4(xv[0], xv[1], xv[2], xv[3]),
-                                         make_float4(xv[4], xv[5], xv[6], xv[7]));
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, aw),
-                                                              __builtin_bit_cast(v8bf, bw), acc,
-                                                              0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    float xv[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const bool ok = rok[i] && k + e < K;
+                        xv[e] = ok ? xr[i][k + e] : 0.f;
+                        if (ok) {
+                            mn = fminf(mn, xv[e]);
+                            mx = fmaxf(mx, xv[e]);
+                        }
+                    }
+                    const v4u aw = pack_bf16(make_float4(xv[0], xv[1], xv[2], xv[3]),
+                                             make_float4(xv[4], xv[5], xv[6], xv[7]));
+#pragma unroll
+                    for (int f = 0; f < NF; ++f)
+                        step(aw, bw[f], acc[i][f]);
+                }
             }
         }
-        // Register v of lane l is row 8*(v/4) + 4*(l/32) + v%4, column l%32.
+        // Register v of lane l is row 4*(l/16) + v, column l%16.
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-            red[wave][v][lane] = acc[v];
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    red[wave][(i * NF + f) * 4 + v][lane] = acc[i][f][v];
         __syncthreads();
-        for (int e = threadIdx.x; e < 32 * 32; e += 64 * kDownWaves) {
-            const int v = e >> 6, l = e & 63;
-            const int orow = rb * 32 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
-            const int ocol = l & 31;
+        for (int e = threadIdx.x; e < NB * NF * 4 * 64; e += 64 * kDownWaves) {
+            const int v = e >> 6, l = e & 63, frag = v >> 2;
+            const int orow = (rb * NB + frag / NF) * 16 + 4 * (l >> 4) + (v & 3);
+            const int ocol = 16 * (frag % NF) + (l & 15);
             float sum = red[0][v][l];
 #pragma unroll
             for (int w = 1; w < kDownWaves; ++w)
@@ -530,20 +573,28 @@ hipError_t launch_lowrank_down(const float *x, int M, int K, const uint16_t *D, 
 {
     const bool fast = (K % 8) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 &&
                       (reinterpret_cast<uintptr_t>(D) & 15) == 0;
-    const int G = grid_for(M, 32, kActPartials);
+    const bool wide = M > 16 * 256;     // more 16-row blocks than compute units
+    const int G = grid_for(M, wide ? 32 : 16, kActPartials);
     if (groups)
         *groups = G;
-    const dim3 g(G), b(64 * kDownWaves);
-    if (part && fast)
-        hipLaunchKernelGGL((k_lowrank_down<true, true>), g, b, 0, stream, x, M, K, D, r, T, part);
-    else if (part)
-        hipLaunchKernelGGL((k_lowrank_down<true, false>), g, b, 0, stream, x, M, K, D, r, T, part);
-    else if (fast)
-        hipLaunchKernelGGL((k_lowrank_down<false, true>), g, b, 0, stream, x, M, K, D, r, T, part);
-    else
-        hipLaunchKernelGGL((k_lowrank_down<false, false>), g, b, 0, stream, x, M, K, D, r, T,
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(G), dim3(64 * kDownWaves), 0, stream, x, M, K, D, r, T,
                            part);
-    return hipGetLastError();
+        return hipGetLastError();
+    };
+    auto with_rows = [&](auto nf, auto nb) {
+        constexpr int NF = decltype(nf)::value, NB = decltype(nb)::value;
+        if (part)
+            return launch(fast ? &k_lowrank_down<true, true, NF, NB>
+                               : &k_lowrank_down<true, false, NF, NB>);
+        return launch(fast ? &k_lowrank_down<false, true, NF, NB>
+                           : &k_lowrank_down<false, false, NF, NB>);
+    };
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
+    if (r <= 16)
+        return wide ? with_rows(One{}, Two{}) : with_rows(One{}, One{});
+    return wide ? with_rows(Two{}, Two{}) : with_rows(Two{}, One{});
 }
 
 hipError_t launch_quantize_activations_lowrank(const float *x, int M, int K, int8_t *q,
