@@ -83,17 +83,18 @@ tasq::XcdRuns cost_runs(const std::vector<LayerDesc> &segs, long long total)
 // Cost of the busiest workgroup of a persistent launch over `runs`.
 double runs_makespan(const std::vector<LayerDesc> &segs, const tasq::XcdRuns &runs)
 {
-    double load[tasq::kListWorkgroups] = {0}, mx = 0;
     constexpr int wgs = tasq::kListWorkgroups / kXcds;
+    double mx = 0;
     size_t l = 0;
-    for (int x = 0; x < kXcds; ++x)
-        for (int u = runs.begin[x]; u < runs.begin[x + 1]; ++u) {
+    for (int x = 0; x < kXcds; ++x) {
+        double load[wgs] = {0};
+        for (int u = runs.begin[x], j = 0; u < runs.begin[x + 1]; ++u, j = (j + 1) % wgs) {
             while (l + 1 < segs.size() && segs[l + 1].tile_begin <= u)
                 ++l;
-            double &w = load[x * wgs + (u - runs.begin[x]) % wgs];
-                w += segs[l].K + kListFixedK;
-            mx = w > mx ? w : mx;
+            load[j] += segs[l].K + kListFixedK;
         }
+        mx = std::max(mx, *std::max_element(load, load + wgs));
+    }
     return mx;
 }
 
@@ -106,26 +107,30 @@ double runs_makespan(const std::vector<LayerDesc> &segs, const tasq::XcdRuns &ru
 // tiles of 256x256, K 640..5120) has 1.42 times the mean work in layer order
 // and 1.09 times with lists.
 // Returns the cost of the busiest workgroup.
+// It is computed on every call, before the first launch, so costs are whole
+// numbers in flat arrays (20 us for the 804 tiles above; 120 with a growing list
+// per workgroup).
 double unit_lists(const std::vector<LayerDesc> &segs, std::vector<uint16_t> &order)
 {
-    constexpr int wgs = tasq::kListWorkgroups / kXcds;
+    constexpr int W = tasq::kListWorkgroups, wgs = W / kXcds;
     std::vector<const LayerDesc *> by_k;
+    by_k.reserve(segs.size());
     for (const LayerDesc &d : segs)
         by_k.push_back(&d);
     std::stable_sort(by_k.begin(), by_k.end(),
                      [](const LayerDesc *a, const LayerDesc *b) { return a->K > b->K; });
-    double load[tasq::kListWorkgroups] = {0}, xload[kXcds] = {0}, mx = 0;
-    std::vector<uint16_t> list[tasq::kListWorkgroups];
-    size_t rows = 0;
+    int load[W] = {0}, rows[W] = {0};
+    long long xload[kXcds] = {0};
+    order.assign((size_t)4 * W, (uint16_t)tasq::kNoUnit);
     for (const LayerDesc *d : by_k) {
         const int n = d->tiles_m * d->tiles_n;
-        const double cost = d->K + kListFixedK;
+        const int cost = d->K + (int)kListFixedK;
         // An eighth of the layer per XCD, the odd tiles to those with the
         // least work so far.
         int take[kXcds];
         for (int x = 0; x < kXcds; ++x) {
             take[x] = n / kXcds;
-            xload[x] += take[x] * cost;
+            xload[x] += (long long)take[x] * cost;
         }
         for (int i = 0; i < n % kXcds; ++i) {
             const int x = (int)(std::min_element(xload, xload + kXcds) - xload);
@@ -135,21 +140,23 @@ double unit_lists(const std::vector<LayerDesc> &segs, std::vector<uint16_t> &ord
         int u = d->tile_begin;
         for (int x = 0; x < kXcds; ++x)
             for (int i = 0; i < take[x]; ++i, ++u) {
-                double *const w = load + x * wgs;
-                const int j = (int)(std::min_element(w, w + wgs) - w);
+                int *const w = load + x * wgs;
+                int least = w[0];
+                for (int j = 1; j < wgs; ++j)
+                    least = w[j] < least ? w[j] : least;
+                int j = 0;
+                while (w[j] != least)
+                    ++j;
                 w[j] += cost;
-                mx = w[j] > mx ? w[j] : mx;
-                // workgroup j of XCD x is block 8 j + x
-                std::vector<uint16_t> &li = list[j * kXcds + x];
-                li.push_back((uint16_t)u);
-                rows = li.size() > rows ? li.size() : rows;
+                const int block = j * kXcds + x;    // workgroup j of XCD x
+                const size_t at = (size_t)rows[block]++ * W + block;
+                if (at + W >= order.size())         // keeps a row of kNoUnit at the end
+                    order.resize(order.size() + 4 * W, (uint16_t)tasq::kNoUnit);
+                order[at] = (uint16_t)u;
             }
     }
-    order.assign((rows + 1) * tasq::kListWorkgroups, (uint16_t)tasq::kNoUnit);
-    for (int w = 0; w < tasq::kListWorkgroups; ++w)
-        for (size_t r = 0; r < list[w].size(); ++r)
-            order[r * tasq::kListWorkgroups + w] = list[w][r];
-    return mx;
+    order.resize((size_t)(*std::max_element(rows, rows + W) + 1) * W);
+    return *std::max_element(load, load + W);
 }
 
 // Heaviest XCD run over the mean, for the per-layer tile order, a tile
