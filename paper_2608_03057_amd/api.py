@@ -52,11 +52,9 @@ def _opts(variant, planes, workspace, split_k, packed=None, act=None, colsums=No
             if k not in _lib.TUNING_FIELDS:
                 raise ValueError(f"unknown tuning field {k}")
             setattr(o, k, int(v))
-    # Fields left out are zero: AUTO, no split, no pointer.
-    if variant:
-        o.variant = variant
-    if split_k:
-        o.split_k = split_k
+    o.variant = variant
+    o.split_k = split_k
+    # Pointers left out are null.
     if planes is not None:
         o.W_planes = planes.data_ptr()
     if workspace is not None:
