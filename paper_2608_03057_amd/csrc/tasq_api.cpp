@@ -1127,6 +1127,8 @@ int tasq_quantize_activations_batch(const tasq_act_job *jobs, int n, void *strea
     hipError_t e = tasq::launch_quantize_activations_batch(js.data(), (int)js.size(),
                                                            static_cast<hipStream_t>(stream));
     return e == hipSuccess ? TASQ_OK : TASQ_ERR_HIP;
+} catch (const std::bad_alloc &) {
+    return TASQ_ERR_HIP;
 }
 
 int tasq_quantize_weights(const float *W, int N, int K, int8_t *W_out, float *alpha_out,

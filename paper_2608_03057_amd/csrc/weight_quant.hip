@@ -19,6 +19,7 @@
 #include "tasq_internal.h"
 
 #include <algorithm>
+#include <new>
 #include <vector>
 
 namespace tasq {
@@ -278,7 +279,7 @@ hipError_t launch_row_sums(const int8_t *X, int M, int K, int32_t *out, hipStrea
 // The batched offline weight quantizer: every job validated as
 // tasq_quantize_weights validates its arguments, before any launch.
 extern "C" int tasq_quantize_weights_batch(const tasq_weight_job *jobs, int n, void *stream)
-{
+try {
     if (n < 0)
         return TASQ_ERR_RANGE;
     if (n == 0)
@@ -309,4 +310,6 @@ extern "C" int tasq_quantize_weights_batch(const tasq_weight_job *jobs, int n, v
         return TASQ_ERR_RANGE;
     hipError_t e = tasq::launch_quantize_weights_batch(jobs, n, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? TASQ_OK : TASQ_ERR_HIP;
+} catch (const std::bad_alloc &) {
+    return TASQ_ERR_HIP;
 }
