@@ -1096,8 +1096,11 @@ int tasq_quantize_activations(const float *x, int M, int K, int8_t *X_out, float
     return e == hipSuccess ? TASQ_OK : TASQ_ERR_HIP;
 }
 
+// The lists of a batch are std::vectors: running out of host memory is returned
+// as TASQ_ERR_HIP, not thrown across the C ABI (here and in
+// tasq_quantize_weights_batch).
 int tasq_quantize_activations_batch(const tasq_act_job *jobs, int n, void *stream)
-{
+try {
     if (n < 0)
         return TASQ_ERR_RANGE;
     if (n == 0)
