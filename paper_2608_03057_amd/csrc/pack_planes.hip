@@ -26,6 +26,10 @@ namespace tasq {
 // one rotate and one AND-OR per plane (nine instructions; bit by bit it was
 // about a hundred).  Bound by memory: 4608x1152 9.4 -> 4.3 us; 10240x3456
 // took 41 us (1.7 TB/s), 10240x6720 now takes 25.0 (5.5 TB/s).
+//
+// FAR: K so large that 32 rows pass the 2 GiB of a window; the chunks are
+// then read by 64-bit addresses.
+template <bool FAR>
 __global__ void __launch_bounds__(256) k_pack_planes(const int8_t *__restrict__ W, int N, int K,
                                                      int KB, int blocks,
                                                      uint32_t *__restrict__ planes)
@@ -35,8 +39,9 @@ __global__ void __launch_bounds__(256) k_pack_planes(const int8_t *__restrict__ 
         return;
     const int nb = blk / KB, kb = blk - nb * KB;
     Window win;
-    win.init(W, N, 32 * nb, 32, K);
-    Chunk5 c[2][2];
+    if constexpr (!FAR)
+        win.init(W, N, 32 * nb, 32, K);
+    Chunk5 c[2][2] = {};
     uint32_t off[2];
     int k0[2];
 #pragma unroll
@@ -45,11 +50,19 @@ __global__ void __launch_bounds__(256) k_pack_planes(const int8_t *__restrict__ 
         const int f = pos & 1, w = (pos >> 1) & 3, r = pos >> 3;
         const int row = 16 * f + r;
         k0[v] = 128 * kb + 64 * (w & 1) + 16 * (w >> 1);
-        off[v] = win.lead + (uint32_t)row * (uint32_t)K + (uint32_t)k0[v];
+        const int8_t *p = W + (size_t)(32 * nb + row) * (size_t)K + k0[v];
+        if constexpr (FAR)
+            off[v] = (uint32_t)reinterpret_cast<uintptr_t>(p);
+        else
+            off[v] = win.lead + (uint32_t)row * (uint32_t)K + (uint32_t)k0[v];
 #pragma unroll
-        for (int sl = 0; sl < 2; ++sl)                  // the word's two sub-steps
-            c[v][sl].load(win.r, 32 * nb + row < N && k0[v] + 32 * sl < K ? off[v] + 32u * sl
-                                                                          : kOOB);
+        for (int sl = 0; sl < 2; ++sl) {                // the word's two sub-steps
+            const bool ok = 32 * nb + row < N && k0[v] + 32 * sl < K;
+            if constexpr (!FAR)
+                c[v][sl].load(win.r, ok ? off[v] + 32u * sl : kOOB);
+            else if (ok)
+                c[v][sl].load_at(p + 32 * sl, W + (size_t)N * (size_t)K);
+        }
     }
     uint32_t *out = planes + ((size_t)nb * 8 * (size_t)KB + (size_t)kb) * 128 + (threadIdx.x & 63);
 #pragma unroll
@@ -78,14 +91,15 @@ __global__ void __launch_bounds__(256) k_pack_planes(const int8_t *__restrict__ 
 hipError_t launch_pack_planes(const int8_t *W, int N, int K, uint32_t *planes,
                               hipStream_t stream)
 {
-    const int KB = (K + 127) / 128;
-    const long long blocks = (long long)((N + 31) / 32) * KB;
+    const int KB = (int)((K + 127LL) / 128);
+    const long long blocks = (N + 31LL) / 32 * KB;
     if (blocks < 1)
         return hipSuccess;
     if (blocks > 0x7fffffffLL)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pack_planes, dim3((unsigned)((blocks + 3) / 4)), dim3(256), 0, stream, W,
-                       N, K, KB, (int)blocks, planes);
+    const auto kernel = window_fits(32, K) ? &k_pack_planes<false> : &k_pack_planes<true>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((blocks + 3) / 4)), dim3(256), 0, stream, W, N, K,
+                       KB, (int)blocks, planes);
     return hipGetLastError();
 }
 

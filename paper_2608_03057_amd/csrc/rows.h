@@ -42,6 +42,14 @@ __device__ __forceinline__ v4i ld16(rsrc_t r, uint32_t off)
 // A call in a row of calls, against byte-by-byte loads (sixteen per chunk):
 // 777x1153 -> 1111 12.6 us (62.5 before, both with 64x64 tiles), 8192x1151 ->
 // 3456 64.2 us (361.7), a 20x30 conv 1275 -> 1280 64.9 us (1217).
+//
+// window_fits: rows * K bytes, the partial dwords at both ends and every
+// offset into them stay below kOOB.
+constexpr bool window_fits(long long rows, long long K)
+{
+    return rows * K + 8 < (long long)kOOB;
+}
+
 struct Window {
     rsrc_t r;
     uint32_t lead;              // bytes before the first row in its dword
@@ -65,6 +73,20 @@ struct Chunk5 {
     {
         lo = ld16(r, off & ~3u);
         hi = __builtin_amdgcn_raw_buffer_load_b32(r, (off & ~3u) + 16u, 0, 0);
+    }
+
+    // The same dwords by address, for rows that no window holds: p < end, and
+    // dwords that begin at or after end, the end of the matrix, are not read.
+    __device__ __forceinline__ void load_at(const int8_t *p, const int8_t *end)
+    {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p) & ~(uintptr_t)3;
+        const uintptr_t e = reinterpret_cast<uintptr_t>(end);
+        const uint32_t *q = reinterpret_cast<const uint32_t *>(a);
+        lo.x = (int)q[0];
+        lo.y = a + 4 < e ? (int)q[1] : 0;
+        lo.z = a + 8 < e ? (int)q[2] : 0;
+        lo.w = a + 12 < e ? (int)q[3] : 0;
+        hi = a + 16 < e ? q[4] : 0u;
     }
 
     // The 16 bytes from byte off % 4 of the five dwords on.
