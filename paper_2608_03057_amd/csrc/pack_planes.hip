@@ -91,16 +91,13 @@ __global__ void __launch_bounds__(256) k_pack_planes(const int8_t *__restrict__ 
 hipError_t launch_pack_planes(const int8_t *W, int N, int K, uint32_t *planes,
                               hipStream_t stream)
 {
-    const int KB = (int)((K + 127LL) / 128);
-    const long long blocks = (N + 31LL) / 32 * KB;
-    if (blocks < 1)
-        return hipSuccess;
-    if (blocks > 0x7fffffffLL)
-        return hipErrorInvalidValue;
     const auto kernel = window_fits(32, K) ? &k_pack_planes<false> : &k_pack_planes<true>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((blocks + 3) / 4)), dim3(256), 0, stream, W, N, K,
-                       KB, (int)blocks, planes);
-    return hipGetLastError();
+    return launch_pack_units(N, K, [&](long long nb, int rows, int KB, int units) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(units + 3) / 4), dim3(256), 0, stream,
+                           W + (size_t)nb * 32 * (size_t)K, rows, K, KB, units,
+                           planes + (size_t)nb * 8 * (size_t)KB * 128);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace tasq

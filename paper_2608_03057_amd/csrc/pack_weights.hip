@@ -44,15 +44,12 @@ __global__ void __launch_bounds__(256) k_pack_weights(const int8_t *__restrict__
 hipError_t launch_pack_weights(const int8_t *W, int N, int K, int8_t *packed,
                                hipStream_t stream)
 {
-    const int KB = (K + 127) / 128;
-    const long long blocks = (long long)((N + 31) / 32) * KB;
-    if (blocks < 1)
-        return hipSuccess;
-    if (blocks > 0x7fffffffLL)
-        return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_pack_weights, dim3((unsigned)((blocks + 3) / 4)), dim3(256), 0, stream,
-                       W, N, K, KB, (int)blocks, packed);
-    return hipGetLastError();
+    return launch_pack_units(N, K, [&](long long nb, int rows, int KB, int units) {
+        hipLaunchKernelGGL(k_pack_weights, dim3((unsigned)(units + 3) / 4), dim3(256), 0, stream,
+                           W + (size_t)nb * 32 * (size_t)K, rows, K, KB, units,
+                           packed + (size_t)nb * (size_t)KB * 4096);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace tasq

@@ -101,6 +101,25 @@ struct Chunk5 {
     }
 };
 
+// Launches of a packer over an N x K weight in blocks of 32 rows: f(nb, rows,
+// KB, units) packs `rows` rows from block nb on, `units` (32-row, 128-byte)
+// units of a wave each.  One launch takes at most 2^22 units or one block of
+// rows, so that its unit and row numbers stay in 32 bits and its threads below
+// the 2^32 of a grid.
+template <class F>
+inline hipError_t launch_pack_units(long long N, long long K, F f)
+{
+    const long long KB = (K + 127) / 128, NB = (N + 31) / 32;
+    const long long most = (1LL << 22) / KB, step = most > 1 ? most : 1;
+    for (long long nb = 0; nb < NB; nb += step) {
+        const long long blocks = NB - nb < step ? NB - nb : step;
+        const long long left = N - 32 * nb, rows = left < 32 * blocks ? left : 32 * blocks;
+        if (hipError_t e = f(nb, (int)rows, (int)KB, (int)(blocks * KB)))
+            return e;
+    }
+    return hipSuccess;
+}
+
 // Keeps the first `valid` bytes of a chunk.
 __device__ __forceinline__ v4i keep_bytes(v4i v, int valid)
 {

@@ -1,6 +1,7 @@
 """Packers at sizes past 32-bit offsets, against the oracle on slices: rows so
 long that 32 of them pass 2 GiB (tasq_pack_planes takes any K), with channels
-missing from the last block and rows at an odd address."""
+missing from the last block and rows at an odd address, and so many rows that
+a packer takes more than one launch."""
 import numpy as np
 import pytest
 import torch
@@ -34,3 +35,19 @@ def test_planes_of_long_rows(N, K, off):
         got = planes[:, :, kb].contiguous().cpu().numpy().view(np.uint32)
         want = np.asarray(oracle.pack_planes(W[:, 128 * kb:128 * (kb + 1)].contiguous().cpu()))
         assert np.array_equal(got.reshape(-1), want.view(np.uint32).reshape(-1)), (N, K, kb)
+
+
+# 2^22 blocks of 32 rows fill one launch.
+@pytest.mark.parametrize("pack", ["planes", "weights"])
+def test_many_rows(pack):
+    N, K = (1 << 27) + 32 + 7, 3
+    W = weight(N, K, 1)
+    NB = (N + 31) // 32
+    out = (T.pack_planes if pack == "planes" else T.pack_weights)(W)
+    torch.cuda.synchronize()
+    out = out.view(torch.uint8).view(NB, 4096)
+    for nb in (0, 1, (1 << 22) - 1, 1 << 22, NB - 1):
+        rows = W[32 * nb:32 * nb + 32].contiguous().cpu()
+        want = (oracle.pack_planes if pack == "planes" else oracle.pack_weights)(rows)
+        want = np.ascontiguousarray(np.asarray(want)).view(np.uint8).reshape(-1)
+        assert np.array_equal(out[nb].cpu().numpy(), want), (pack, nb)
