@@ -725,11 +725,13 @@ __device__ __forceinline__ void cols_request(const LayerDesc &d, int n0, int bit
 {
     const int lane = threadIdx.x & 63;
     const int wn = (threadIdx.x >> 6) % C::WAVES_N;
-    const uint32_t nb = (uint32_t)d.N * 4u;
+    // Only y has factors: without it the caller's pointers to them, which need
+    // not be there (act_params without colsums), are not read.
+    const uint32_t nb = d.y ? (uint32_t)d.N * 4u : 0u;
     const rsrc_t rsw = make_rsrc(d.sw, d.sw ? nb : 0u);
     const rsrc_t rbias = make_rsrc(d.bias, d.bias ? nb : 0u);
     const rsrc_t rcs = make_rsrc(d.colsums, d.act ? 8u * nb : 0u);
-    const rsrc_t ract = make_rsrc(d.act, d.act ? 8u : 0u);
+    const rsrc_t ract = make_rsrc(d.act, d.act && d.y ? 8u : 0u);
     cl.alpha = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ract, 0, 0, 0));
     cl.zx = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ract, 4, 0, 0));
 #pragma unroll
@@ -745,7 +747,7 @@ __device__ __forceinline__ void cols_request(const LayerDesc &d, int n0, int bit
         cl.wz[j] = 0.f;
         if constexpr (EXTRAS) {
             // weight zero points z_n, read only when the epilogue adds their term
-            const rsrc_t rwz = make_rsrc(d.wz, d.wz && d.y ? nb : 0u);
+            const rsrc_t rwz = make_rsrc(d.wz, d.wz ? nb : 0u);
             cl.wz[j] =
                 __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rwz, on, 0, 0));
         }
