@@ -581,15 +581,16 @@ __device__ __forceinline__ void split_bf16(float t, uint32_t &hi, uint32_t &lo)
 
 // Stages the tile's low-rank operands in LDS: T rows m0.. (fp32 [M][r],
 // split into bfloat16 hi and lo parts) and U rows n0.. (bfloat16 [N][r]).
-// Rows past M or N read zero through the buffer bounds.
-template <class C>
+// Rows past M or N read zero through the buffer bounds.  NT threads take part,
+// each element by one of them.
+template <class C, int NT = C::NT>
 __device__ __forceinline__ void stage_lowrank(const LayerDesc &d, int m0, int n0, char *lds)
 {
     const int r = d.lr_r;
     const rsrc_t rU = make_rsrc(d.lr_U, (uint32_t)d.N * (uint32_t)r * 2u);
     char *Thi = lds, *Tlo = lds + C::BM * kLrPitch, *Us = lds + 2 * C::BM * kLrPitch;
     const int tpr = r / 4;
-    for (int e = threadIdx.x; e < C::BM * tpr; e += C::NT) {
+    for (int e = threadIdx.x; e < C::BM * tpr; e += NT) {
         const int row = e / tpr, c = e % tpr;
         // A plain float4 load: the components of a 16-byte buffer load taken
         // apart one by one here compiled to one dword load used four times.
@@ -607,7 +608,7 @@ __device__ __forceinline__ void stage_lowrank(const LayerDesc &d, int m0, int n0
             make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
     }
     const int upr = r / 8;
-    for (int e = threadIdx.x; e < C::BN * upr; e += C::NT) {
+    for (int e = threadIdx.x; e < C::BN * upr; e += NT) {
         const int row = e / upr, c = e % upr;
         *reinterpret_cast<v4i *>(Us + row * kLrPitch + 16 * c) =
             ld16(rU, ((uint32_t)(n0 + row) * (uint32_t)r + 8u * c) * 2u);
@@ -617,12 +618,12 @@ __device__ __forceinline__ void stage_lowrank(const LayerDesc &d, int m0, int n0
 // Stages, per tile row m, the activation sum that multiplies a weight zero
 // point: R[m] = sum_k x_code[m][k] (+ K (128 - z_x) for asymmetric codes,
 // whose x_hat carries the offset 128 - z_x in every element).
-template <class C>
+template <class C, int NT = C::NT>
 __device__ __forceinline__ void stage_rowsums(const LayerDesc &d, int m0, char *lds)
 {
     float *R = reinterpret_cast<float *>(lds + (2 * C::BM + C::BN) * kLrPitch);
     const float off = d.act ? (float)d.K * (128.0f - d.act[1]) : 0.0f;
-    for (int e = threadIdx.x; e < C::BM; e += C::NT)
+    for (int e = threadIdx.x; e < C::BM; e += NT)
         R[e] = m0 + e < d.M ? (float)d.xrs[m0 + e] + off : 0.0f;
 }
 
@@ -690,7 +691,7 @@ struct EpiCols {
     uint32_t base[C::FN];   // byte offset of (row mrow, column n), kOOB past N
 };
 
-template <class C>
+template <class C, int NT = C::NT>
 __device__ __forceinline__ void epilogue_stage(const LayerDesc &d, int m0, int n0, char *lds)
 {
     const bool lowrank = d.lr_T != nullptr && d.y != nullptr;
@@ -698,9 +699,9 @@ __device__ __forceinline__ void epilogue_stage(const LayerDesc &d, int m0, int n
     if (lowrank || wzero) {
         __syncthreads();            // every wave is done with the main loop's LDS
         if (lowrank)
-            stage_lowrank<C>(d, m0, n0, lds);
+            stage_lowrank<C, NT>(d, m0, n0, lds);
         if (wzero)
-            stage_rowsums<C>(d, m0, lds);
+            stage_rowsums<C, NT>(d, m0, lds);
         __syncthreads();
     }
 }

@@ -64,7 +64,7 @@ __device__ __forceinline__ void kg_tile(const LayerDesc &d, int t, int bits, v4i
                         acc[i][j][v] += p[((i * C::FN + j) * 16 + v) * C::NT];
         }
     }
-    epilogue_stage<C>(d, m0, n0, reinterpret_cast<char *>(sm));
+    epilogue_stage<C, KG * C::NT>(d, m0, n0, reinterpret_cast<char *>(sm));
     if (group == 0) {
         EpiCols<C> ec;
         cols_finish<C, true>(d, m0, n0, cl, ec);
