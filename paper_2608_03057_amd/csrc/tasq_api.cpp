@@ -902,7 +902,9 @@ int static_scratch(hipStream_t stream, void **out)
 }
 
 // Host bytes to device memory, stream-ordered: by value in the arguments of
-// up to kUploadLaunches small launches, or as one copy.  A copy from pageable
+// up to kUploadLaunches small launches, or as one copy; under capture always by
+// value, because a captured copy reads its source again at every replay, when
+// the host lists are gone.  A copy from pageable
 // memory is staged by the runtime and costs the caller as much as several
 // launches: 20 layers of a 16-token schedule, 4 steps, 22.6 us of host time
 // against 28.6 with two copies; one layer, 1 step, 11.2 against 15.9.
@@ -922,8 +924,13 @@ __global__ void k_upload(uint4 *dst, int n, UploadChunk c)
 // dst 16-byte aligned, bytes a multiple of 16.
 hipError_t upload(void *dst, const void *src, size_t bytes, hipStream_t stream)
 {
-    if (bytes > kUploadLaunches * kUploadChunk)
-        return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, stream);
+    if (bytes > kUploadLaunches * kUploadChunk) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipError_t e = hipStreamIsCapturing(stream, &capture))
+            return e;
+        if (capture == hipStreamCaptureStatusNone)
+            return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, stream);
+    }
     for (size_t off = 0; off < bytes; off += kUploadChunk) {
         const size_t n = std::min(bytes - off, kUploadChunk);
         UploadChunk c;
