@@ -287,14 +287,18 @@ int persistent_parties(const tasq_opts *o, int wgs_per_xcd)
 // 256x256) 36.1 / 33.7, 8192x1152 -> 3456 (448) 42.1 / 49.7, 8192x1152 -> 4608
 // (576) 51.1 / 66.3, 4096x2240 -> 11200 (704) 109.3 / 115.4, 6278x11200 -> 3456
 // (350) 229 / 259, 8192x8192 -> 8192 462 / 435.
-int pick_packed_tile(const tasq_opts *o, long long M, long long N, long long K)
+// A conv's taps need more registers than the 128x256 tile leaves (its conv
+// kernel spills): 256x256 from 140 tiles up whatever their number (us, 128x256 /
+// 256x256: 96x96 pixels 1280 -> 2560 434 / 303, 160x160 640 -> 640 187 / 153,
+// 128x128 320 -> 1280 99.5 / 91.6).
+int pick_packed_tile(const tasq_opts *o, long long M, long long N, long long K, bool conv)
 {
     const int f = forced_ptile(o);
     if (f >= 0)
         return f;
     const long long t256 = ((M + 255) / 256) * ((N + 255) / 256);
     const long long t128x256 = ((M + 127) / 128) * ((N + 255) / 256);
-    if ((t256 >= 140 && t256 <= kComputeUnits) || M * N * K >= (1LL << 38))
+    if ((t256 >= 140 && (conv || t256 <= kComputeUnits)) || M * N * K >= (1LL << 38))
         return tasq::PTILE_256x256_K128_W8;
     if (t128x256 >= 200)
         return tasq::PTILE_128x256_K128_W4;
@@ -660,7 +664,8 @@ int launch_layer(const LayerDesc &d, const tasq_opts *o, hipStream_t stream,
         return e == hipSuccess ? TASQ_OK : TASQ_ERR_HIP;
     }
     if (wsrc == SRC_PACKED && packed_fits(d)) {
-        e = tasq::packed_tile_ops(pick_packed_tile(o, d.M, d.N, d.K))
+        e = tasq::packed_tile_ops(
+                pick_packed_tile(o, d.M, d.N, d.K, d.kind == tasq::KIND_CONV3X3))
                 .single(d, x_aligned(d), stream);
         return e == hipSuccess ? TASQ_OK : TASQ_ERR_HIP;
     }
