@@ -320,18 +320,27 @@ int pick_packed_grouped_tile(const tasq_opts *o)
 //   128x128 (two workgroups per compute unit): rounds of 512 tiles of 4 +
 //     1.15 nk, which overlap from two rounds on; a last round of at most one
 //     workgroup per compute unit runs at 0.65 nk.
-double cost_256(long long tiles, long long nk)
+// With a low-rank branch of rank 32 a round ends 3.5 and 3.0 us later (its
+// operands staged and multiplied; a round of half the slots is as long), which
+// moves the line (us, 128x128 / 256x256: 3000x1152 -> 3456 25.6 / 23.5, 777x1280 ->
+// 10240 24.7 / 22.1).  At rank 16 and with weight zero points both grow by less
+// and alike, and the line stays.
+double cost_256(long long tiles, long long nk, bool rank32)
 {
-    return (double)((tiles + kComputeUnits - 1) / kComputeUnits) * (8.5 + 1.35 * nk);
+    const double end = rank32 ? 12.0 : 8.5;
+    return (double)((tiles + kComputeUnits - 1) / kComputeUnits) * (end + 1.35 * nk);
 }
 
-double cost_128(long long tiles, long long nk)
+double cost_128(long long tiles, long long nk, bool rank32)
 {
     const long long slots = 2 * kComputeUnits, full = tiles / slots, rem = tiles % slots;
+    const double end = rank32 ? 7.0 : 4.0;
     if (full >= 2)
         return (double)tiles / slots * (4.0 + 1.15 * nk);
     const double last = rem == 0 ? 0.0 : rem <= kComputeUnits ? 0.65 * nk : 1.15 * nk;
-    return (full ? 4.0 + 1.15 * nk : 4.0) + last;
+    if (!full)
+        return end + last;
+    return end + 1.15 * nk + last + (rem && rank32 ? 3.0 : 0.0);
 }
 
 // Tile used for a single (non-grouped) launch: 64x64 tiles, so that more
@@ -345,7 +354,8 @@ double cost_128(long long tiles, long long nk)
 // (8192x1151 -> 3456 64 us against 69), and none for a conv, whose chunks'
 // taps and shifts need more registers than that tile leaves (96x96 pixels
 // 650 -> 650: 93.8 us with 128x128 tiles, 152 with 256x256, 95.9 with 64x64).
-int pick_tile(const tasq_opts *o, long long M, long long N, long long K, bool aligned, bool conv)
+int pick_tile(const tasq_opts *o, long long M, long long N, long long K, bool aligned, bool conv,
+              bool rank32)
 {
     const int f = forced_tile(o);
     if (f >= 0)
@@ -353,7 +363,8 @@ int pick_tile(const tasq_opts *o, long long M, long long N, long long K, bool al
     const long long t256 = ((M + 255) / 256) * ((N + 255) / 256);
     const long long t128 = ((M + 127) / 128) * ((N + 127) / 128);
     const long long nk = (K + 127) / 128;
-    const bool big = aligned && !conv ? cost_256(t256, nk) < cost_128(t128, nk)
+    const bool big = aligned && !conv ? cost_256(t256, nk, rank32) <
+                                            cost_128(t128, nk, rank32)
                                       : t256 >= 140 && (aligned || !conv);
     if (t128 >= 200 && big)
         return tasq::TILE_256x256_K128_W8_PF1;
