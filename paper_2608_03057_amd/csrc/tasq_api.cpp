@@ -424,18 +424,6 @@ int auto_splits(long long M, long long N, long long K)
     return s >= 2 ? (int)s : 1;
 }
 
-// The ranges actually taken, at most those the workspace is sized for: enough
-// that 128x128 tiles times ranges fill the two workgroups per compute unit
-// and no more, each range's partial output being written and read again (the
-// conv above, 80 tiles of 128x128: 6 ranges 32.6 us, 4 37.5, 3 37.5, 2 47.8;
-// 256x256 tiles with 10 ranges 39.4).
-int chosen_splits(long long M, long long N, long long K)
-{
-    const long long t128 = ((M + 127) / 128) * ((N + 127) / 128);
-    const long long s = std::max(2LL, 2LL * kComputeUnits / t128);
-    return (int)std::min<long long>(s, auto_splits(M, N, K));
-}
-
 // K range per split (a multiple of 128, the largest BK) and the resulting
 // number of non-empty splits.
 void split_geometry(int K, int s, int &kchunk, int &splits)
@@ -473,10 +461,54 @@ constexpr size_t schedule_partials_offset(int L)
            round_up((size_t)L * 64, kWsAlign);
 }
 
-int pick_split_tile(const tasq_opts *o)
+// Estimated us of a layer cut into s ranges of K, fitted to 60 layers
+// (convs of 8x8 to 64x96 pixels, linear layers of 65 to 4096 rows, K 8192..32768;
+// most within 15%): rounds of the chip's workgroups, a range's nk K tiles each,
+// and the partial outputs written and read again, 0.42 to 0.47 us per MB.  A
+// linear layer's 128x128 tiles read its operands at 12 TB/s at best (a conv's
+// taps find theirs again nearby).
+double split_cost(int tile, long long M, long long N, int K, int s, bool conv)
 {
-    const int f = forced_tile(o);
-    return f >= 0 ? f : tasq::TILE_128x128_K128_W4_PF2;
+    int kchunk, splits;
+    split_geometry(K, s, kchunk, splits);
+    const int b = tile == tasq::TILE_256x256_K128_W8_PF1 ? 256 : 128;
+    const double tiles = (double)((M + b - 1) / b) * ((N + b - 1) / b);
+    const double wgs = tiles * splits, nk = kchunk / 128, mb = 4e-6 * M * N * splits;
+    if (b == 256)
+        return std::ceil(wgs / kComputeUnits) * (6.0 + 1.5 * nk) + 0.42 * mb;
+    const double rounds = wgs <= kComputeUnits
+                              ? 5.8 + 0.67 * nk
+                              : std::max(1.0, wgs / (2 * kComputeUnits)) * (2.0 + 1.1 * nk);
+    const double reads = conv ? 0.0 : tiles * 256 * K / 12e6;
+    return std::max(rounds, reads) + 0.47 * mb;
+}
+
+// Tile and ranges of a split layer, s >= 2 as the caller forces it, 0 = the
+// library's choice among two: 128x128 tiles with as many ranges as fill the two
+// workgroups per compute unit, or 256x256 tiles with as many as fill one, which
+// the workspace is sized for.  The first has fewer workgroups per range to
+// feed and fewer partials, the second reads its operands half as often.
+// us, 128x128 / 256x256: 32x32 pixels 1280 -> 1280 32.5 (6 ranges) / 37.6 (10),
+// 48x48 1280 -> 1280 62.6 (2) / 57.7 (5), 48x48 2560 -> 1280 110.8 / 90.0, 40x40
+// 2560 -> 1280 80.3 (3) / 71.6 (7), 64x64 1280 -> 640 51.2 (3) / 57.3 (5), linear
+// 1024x32768 -> 1024 59.5 (8) / 52.3 (16), 4096x32768 -> 1024 162.8 (2) / 136.2 (4).
+struct SplitForm {
+    int tile, s;
+};
+
+SplitForm pick_split(const tasq_opts *o, long long M, long long N, int K, int s, bool conv)
+{
+    const long long t128 = ((M + 127) / 128) * ((N + 127) / 128);
+    const int most = s ? s : auto_splits(M, N, K);
+    const int fill = s ? s : (int)std::min<long long>(std::max(2LL, 2LL * kComputeUnits / t128),
+                                                      most);
+    const SplitForm small = {tasq::TILE_128x128_K128_W4_PF2, fill};
+    const SplitForm big = {tasq::TILE_256x256_K128_W8_PF1, most};
+    if (const int f = forced_tile(o); f >= 0)
+        return {f, fill};
+    return split_cost(big.tile, M, N, K, big.s, conv) < split_cost(small.tile, M, N, K, small.s, conv)
+               ? big
+               : small;
 }
 
 // Tiles of the grouped per-step launch.
@@ -693,16 +725,19 @@ int launch_layer(const LayerDesc &d, const tasq_opts *o, hipStream_t stream,
         // Split-K: forced (split_k >= 2, needs the workspace) or chosen
         // (split_k == 0, only with a workspace of tasq_workspace_bytes).
         const int req = o ? o->split_k : 0;
-        int splits = 1, kchunk = 0;
+        int splits = 1, kchunk = 0, split_tile = 0;
         if (allow_split && req != 1 && d.K > 128) {
             const unsigned long long room = o && o->workspace ? o->workspace_bytes : 0;
             int s = req;
             if (req == 0) {
                 const size_t whole = tasq_workspace_bytes(d.M, d.N, d.K);
-                s = whole && room >= whole ? chosen_splits(d.M, d.N, d.K) : 1;
+                s = whole && room >= whole ? 0 : 1;
             }
-            if (s > 1) {
-                split_geometry(d.K, s, kchunk, splits);
+            if (s != 1) {
+                const SplitForm form =
+                    pick_split(o, d.M, d.N, d.K, s, d.kind == tasq::KIND_CONV3X3);
+                split_tile = form.tile;
+                split_geometry(d.K, form.s, kchunk, splits);
                 const unsigned long long need = 4ULL * splits * (unsigned long long)d.M * d.N;
                 const bool ws_ok = room >= need && need < (1ULL << 31);
                 if (!ws_ok && req >= 2)
@@ -713,7 +748,7 @@ int launch_layer(const LayerDesc &d, const tasq_opts *o, hipStream_t stream,
         }
         if (splits > 1) {
             int32_t *part = static_cast<int32_t *>(o->workspace);
-            e = tasq::tile_ops(pick_split_tile(o)).split(d, part, splits, kchunk, stream);
+            e = tasq::tile_ops(split_tile).split(d, part, splits, kchunk, stream);
             if (e == hipSuccess)
                 e = tasq::launch_split_finish(d, part, splits, stream);
         } else {
