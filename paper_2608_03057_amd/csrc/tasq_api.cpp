@@ -336,7 +336,7 @@ double cost_128(long long tiles, long long nk, bool rank32)
     const long long slots = 2 * kComputeUnits, full = tiles / slots, rem = tiles % slots;
     const double end = rank32 ? 7.0 : 4.0;
     if (full >= 2)
-        return (double)tiles / slots * (4.0 + 1.15 * nk);
+        return (double)tiles / slots * (end + 1.15 * nk);
     const double last = rem == 0 ? 0.0 : rem <= kComputeUnits ? 0.65 * nk : 1.15 * nk;
     if (!full)
         return end + last;
@@ -756,7 +756,8 @@ int launch_layer(const LayerDesc &d, const tasq_opts *o, hipStream_t stream,
             const bool conv = d.kind == tasq::KIND_CONV3X3;
             e = kg != tasq::KG_NONE
                     ? tasq::launch_kgroups(d, kg, aligned, stream)
-                    : tasq::tile_ops(pick_tile(o, d.M, d.N, d.K, aligned, conv))
+                    : tasq::tile_ops(pick_tile(o, d.M, d.N, d.K, aligned, conv,
+                                               d.y && d.lr_T && d.lr_r > 16))
                           .single(d, aligned, stream);
         }
     }
