@@ -891,8 +891,8 @@ __device__ __forceinline__ void pin(LayerDesc &d)
                       "+s"(d.act), "+s"(d.colsums), "+s"(d.lr_T), "+s"(d.lr_U), "+s"(d.wz),
                       "+s"(d.xrs), "+s"(d.acc), "+s"(d.y), "+s"(d.sx), "+s"(d.M), "+s"(d.N),
                       "+s"(d.K), "+s"(d.H), "+s"(d.Wd), "+s"(d.C), "+s"(d.bits), "+s"(d.lr_r),
-                      "+s"(d.tiles_m), "+s"(d.tiles_n), "+s"(d.tile_begin), "+s"(d.tile_first),
-                      "+s"(d.layer), "+s"(d.kind));
+                      "+s"(d.tiles_m), "+s"(d.tiles_n), "+s"(d.tile_begin), "+s"(d.layer),
+                      "+s"(d.kind));
 }
 
 template <class C, bool ALIGNED, int KIND, bool PLANES>
@@ -922,14 +922,16 @@ __device__ __forceinline__ int table_bits(const uint8_t *table, int idx)
     return (int)((w >> (8 * (idx & 3))) & 0xffu);
 }
 
-// Segment (run of one layer's tiles) of work unit t in a grouped launch:
-// the last segment whose first unit is at or before t.
-__device__ __forceinline__ int find_segment(const LayerDesc *__restrict__ descs, int L, int t)
+// Layer of a work unit in a grouped launch: the last one whose first unit,
+// as key gives it, is at or before t.
+template <class Key>
+__device__ __forceinline__ int find_layer(const LayerDesc *__restrict__ descs, int L, int t,
+                                          const Key &key)
 {
     int lo = 0, hi = L - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (descs[mid].tile_begin <= t)
+        if (key(descs[mid].tile_begin) <= t)
             lo = mid;
         else
             hi = mid - 1;
@@ -937,26 +939,64 @@ __device__ __forceinline__ int find_segment(const LayerDesc *__restrict__ descs,
     return lo;
 }
 
-// Grouped launch over every layer of one denoising step: workgroup t finds
-// its segment (a run of one layer's tiles) by binary search over the
-// segments' first work units, and the layer's b from the (layer, stage)
-// table (App. G.1: a table lookup, no re-launch).  CONV adds the
+__device__ __forceinline__ int find_layer(const LayerDesc *__restrict__ descs, int L, int t)
+{
+    return find_layer(descs, L, t, [](int begin) { return begin; });
+}
+
+// Work unit of this workgroup in a grouped launch with one workgroup per
+// tile: its layer, and the tile within it.  Each XCD walks either one
+// contiguous run of the layers' tiles in order (xcd_remap), or, with rounds,
+// an eighth of every layer in turn: unit p of the layer order counts towards
+// XCD p % 8, and the units of a layer that count towards one XCD stand for a
+// contiguous run of the layer's tiles, the XCDs' runs one after the other.
+// (Cut on the host into eight descriptors per layer, the list of 32 layers
+// was 45 KB and its copy held a call of one step up by 13 us.)
+struct GroupedUnit {
+    int layer, tile;
+};
+
+__device__ __forceinline__ GroupedUnit grouped_unit(const LayerDesc *__restrict__ descs, int L,
+                                                    int rounds)
+{
+    GroupedUnit u;
+    if (!rounds) {
+        const int t = xcd_remap(blockIdx.x, gridDim.x);
+        u.layer = find_layer(descs, L, t);
+        u.tile = t - descs[u.layer].tile_begin;
+        return u;
+    }
+    const unsigned x = blockIdx.x % 8, q = blockIdx.x / 8;
+    // Units below p that count towards XCD x, and towards the XCDs before it.
+    auto own = [&](unsigned p) { return (p + 7 - x) / 8; };
+    auto before = [&](unsigned p) { return p / 8 * x + min(p % 8, x); };
+    u.layer = find_layer(descs, L, (int)q, [&](int begin) { return (int)own((unsigned)begin); });
+    const LayerDesc &d = descs[u.layer];
+    const unsigned p = (unsigned)d.tile_begin, n = (unsigned)d.tiles_m * (unsigned)d.tiles_n;
+    u.tile = (int)(before(p + n) - before(p) + q - own(p));
+    return u;
+}
+
+// Grouped launch over every layer of one denoising step: a workgroup finds
+// its layer by binary search over the layers' first work units, and the
+// layer's b from the (layer, stage) table (App. G.1: a table lookup, no
+// re-launch).  CONV adds the
 // implicit-GEMM path for 3x3 conv layers; without it every layer must be
 // linear.
 template <class C, bool CONV>
 __global__ void __launch_bounds__(C::NT, C::OCC)
 k_masked_gemm_grouped(const LayerDesc *__restrict__ descs, int L, const uint8_t *table, int S,
-                      int stage)
+                      int stage, int rounds)
 {
     __shared__ v4i smA[C::SMA];
     __shared__ v4i smB[C::NSTAGE * C::BN * C::CPR];
-    const int t = xcd_remap(blockIdx.x, gridDim.x);
-    LayerDesc d = descs[find_segment(descs, L, t)];
+    const GroupedUnit u = grouped_unit(descs, L, rounds);
+    LayerDesc d = descs[u.layer];
     pin(d);
     const int bits = table_bits(table, d.layer * S + stage);
     const uint32_t wmask = keep_mask_dword(bits);
     int tm, tn;
-    tile_coords(t - d.tile_begin + d.tile_first, d.tiles_m, d.tiles_n, tm, tn);
+    tile_coords(u.tile, d.tiles_m, d.tiles_n, tm, tn);
     const int m0 = tm * C::BM, n0 = tn * C::BN;
     v16i acc[C::FM][C::FN];
     ColLoads<C> cl;
@@ -987,7 +1027,7 @@ template <class C>
 __device__ __forceinline__ void unit_coords(const LayerDesc &d, int t, int &m0, int &n0)
 {
     int tm, tn;
-    tile_coords(t - d.tile_begin + d.tile_first, d.tiles_m, d.tiles_n, tm, tn);
+    tile_coords(t - d.tile_begin, d.tiles_m, d.tiles_n, tm, tn);
     m0 = tm * C::BM;
     n0 = tn * C::BN;
 }
@@ -1034,7 +1074,7 @@ k_masked_gemm_persistent(const LayerDesc *__restrict__ descs, int L, int total, 
     };
     auto bits_of = [&](int sg) { return table_bits(table, descs[sg].layer * S + stage); };
 
-    int seg = find_segment(descs, L, u);
+    int seg = find_layer(descs, L, u);
     int m0, n0;
     unit_coords<C>(descs[seg], u, m0, n0);
     int bits = bits_of(seg);
@@ -1072,7 +1112,7 @@ k_masked_gemm_persistent(const LayerDesc *__restrict__ descs, int L, int total, 
         // no register set is live around the tile loop.)
         constexpr int JH = C::FN / 2;
         const LayerDesc &dp = d;
-        seg = find_segment(descs, L, u);
+        seg = find_layer(descs, L, u);
         unit_coords<C>(descs[seg], u, m0, n0);
         bits = bits_of(seg);
         __builtin_amdgcn_sched_barrier(0);
@@ -1188,15 +1228,15 @@ hipError_t launch_planes_cfg(const LayerDesc &din, bool aligned, hipStream_t str
 template <class C>
 hipError_t launch_grouped_cfg(const LayerDesc *d_descs, int L, int total_tiles,
                               const uint8_t *d_table, int S, int stage, bool any_conv,
-                              hipStream_t stream)
+                              bool rounds, hipStream_t stream)
 {
     dim3 g((unsigned)total_tiles), b(C::NT);
     if (any_conv)
         hipLaunchKernelGGL((k_masked_gemm_grouped<C, true>), g, b, 0, stream, d_descs, L, d_table,
-                           S, stage);
+                           S, stage, rounds ? 1 : 0);
     else
         hipLaunchKernelGGL((k_masked_gemm_grouped<C, false>), g, b, 0, stream, d_descs, L,
-                           d_table, S, stage);
+                           d_table, S, stage, rounds ? 1 : 0);
     return hipGetLastError();
 }
 

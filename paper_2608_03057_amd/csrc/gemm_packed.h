@@ -221,16 +221,16 @@ __global__ void __launch_bounds__(C::NT, C::OCC) k_gemm_packed(LayerDesc d)
 template <class C, bool CONV>
 __global__ void __launch_bounds__(C::NT, C::OCC)
 k_gemm_packed_grouped(const LayerDesc *__restrict__ descs, int L, const uint8_t *table, int S,
-                      int stage)
+                      int stage, int rounds)
 {
     __shared__ v4i sm[C::SM];
-    const int t = xcd_remap(blockIdx.x, gridDim.x);
-    LayerDesc d = descs[find_segment(descs, L, t)];
+    const GroupedUnit u = grouped_unit(descs, L, rounds);
+    LayerDesc d = descs[u.layer];
     pin(d);
     const int bits = table_bits(table, d.layer * S + stage);
     const uint32_t wmask = keep_mask_dword(bits);
     int tm, tn;
-    tile_coords(t - d.tile_begin + d.tile_first, d.tiles_m, d.tiles_n, tm, tn);
+    tile_coords(u.tile, d.tiles_m, d.tiles_n, tm, tn);
     const int m0 = tm * C::BM, n0 = tn * C::BN;
     v16i acc[C::FM][C::FN];
     ColLoads<C> cl;
@@ -267,15 +267,15 @@ hipError_t launch_packed_single(const LayerDesc &din, bool aligned, hipStream_t 
 template <class C>
 hipError_t launch_packed_grouped(const LayerDesc *d_descs, int L, int total_tiles,
                                  const uint8_t *d_table, int S, int stage, bool any_conv,
-                                 hipStream_t stream)
+                                 bool rounds, hipStream_t stream)
 {
     dim3 g((unsigned)total_tiles), b(C::NT);
     if (any_conv)
         hipLaunchKernelGGL((k_gemm_packed_grouped<C, true>), g, b, 0, stream, d_descs, L,
-                           d_table, S, stage);
+                           d_table, S, stage, rounds ? 1 : 0);
     else
         hipLaunchKernelGGL((k_gemm_packed_grouped<C, false>), g, b, 0, stream, d_descs, L,
-                           d_table, S, stage);
+                           d_table, S, stage, rounds ? 1 : 0);
     return hipGetLastError();
 }
 

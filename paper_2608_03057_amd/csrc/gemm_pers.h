@@ -157,7 +157,7 @@ struct StepLayers {
     const uint8_t *__restrict__ table;
     int L, S, stage;
 
-    __device__ __forceinline__ int find(int u) const { return find_segment(descs, L, u); }
+    __device__ __forceinline__ int find(int u) const { return find_layer(descs, L, u); }
     __device__ __forceinline__ const LayerDesc &desc(int seg) const { return descs[seg]; }
     __device__ __forceinline__ int bits(int seg) const
     {
@@ -515,7 +515,7 @@ hipError_t launch_single_ds(const LayerDesc &din, bool aligned, hipStream_t stre
     const long long tiles = (long long)d.tiles_m * d.tiles_n;
     if (tiles > 0x7fffffffLL)
         return hipErrorInvalidValue;
-    d.tile_begin = d.tile_first = 0;
+    d.tile_begin = 0;
     XcdRuns runs;
     for (int x = 0; x <= 8; ++x)
         runs.begin[x] = (int)(tiles * x / 8);

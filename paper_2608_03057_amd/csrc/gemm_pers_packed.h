@@ -55,7 +55,7 @@ __device__ __forceinline__ void kpos_enter(const LayerDesc *__restrict__ descs, 
         p.nk = 1;
         return;
     }
-    p.seg = find_segment(descs, L, p.u);
+    p.seg = find_layer(descs, L, p.u);
     unit_coords<C>(descs[p.seg], p.u, p.m0, p.n0);
     // (a layer with K = 0 still takes one K tile, of zero operands, so that
     // its outputs are written)

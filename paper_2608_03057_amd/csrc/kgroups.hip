@@ -87,14 +87,14 @@ __global__ void __launch_bounds__(C::NT * KG, C::OCC) k_masked_gemm_kg(LayerDesc
 template <class C, int KG>
 __global__ void __launch_bounds__(C::NT * KG, C::OCC)
 k_masked_gemm_kg_grouped(const LayerDesc *__restrict__ descs, int L,
-                         const uint8_t *__restrict__ table, int S, int stage)
+                         const uint8_t *__restrict__ table, int S, int stage, int rounds)
 {
     __shared__ v4i sm[kg_lds<C, KG>()];
-    const int u = xcd_remap(blockIdx.x, gridDim.x);
-    LayerDesc d = descs[find_segment(descs, L, u)];
+    const GroupedUnit u = grouped_unit(descs, L, rounds);
+    LayerDesc d = descs[u.layer];
     pin(d);
     const int bits = table_bits(table, d.layer * S + stage);
-    kg_tile<C, KG, true, KIND_LINEAR>(d, u - d.tile_begin + d.tile_first, bits, sm);
+    kg_tile<C, KG, true, KIND_LINEAR>(d, u.tile, bits, sm);
 }
 
 template <class C, int KG>
@@ -131,13 +131,13 @@ hipError_t launch_kgroups(const LayerDesc &d, KGroupTile tile, bool aligned, hip
 
 hipError_t launch_kgroups_2x64(const LayerDesc *d_descs, int L, int total_tiles,
                                const uint8_t *d_table, int S, int stage, bool any_conv,
-                               hipStream_t stream)
+                               bool rounds, hipStream_t stream)
 {
     using C = Cfg<64, 64, 128, 2, 2, 2, 4>;
     if (any_conv)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_masked_gemm_kg_grouped<C, 2>), dim3((unsigned)total_tiles),
-                       dim3(C::NT * 2), 0, stream, d_descs, L, d_table, S, stage);
+                       dim3(C::NT * 2), 0, stream, d_descs, L, d_table, S, stage, rounds ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -357,7 +357,7 @@ k_skinny_grouped(const LayerDesc *__restrict__ descs, int L, const uint8_t *tabl
     }
     const LayerDesc d = descs[lo];
     skinny_block<SRC, MT, SK_WAVES_GROUPED>(d, table[d.layer * S + stage],
-                                            t - d.tile_begin + d.tile_first, red);
+                                            t - d.tile_begin, red);
 }
 
 // Token tiles of 16 rows for M rows (M <= 64).

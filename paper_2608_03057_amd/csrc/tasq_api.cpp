@@ -52,15 +52,15 @@ constexpr double kListFixedK = 680.0;
 // a tile costing its K plus kTileFixedK.  Equal counts of tiles would give
 // the XCD whose run ends a block later in the 28-block PixArt-shaped step
 // (more 4608-deep tiles) 3% more work than the mean.
-tasq::XcdRuns cost_runs(const std::vector<LayerDesc> &segs, long long total)
+tasq::XcdRuns cost_runs(const std::vector<LayerDesc> &descs, long long total)
 {
     double all = 0;
-    for (const LayerDesc &d : segs)
+    for (const LayerDesc &d : descs)
         all += (double)d.tiles_m * d.tiles_n * ((double)d.K + kTileFixedK);
     tasq::XcdRuns r = {};
     int x = 1;
     double cum = 0;
-    for (const LayerDesc &d : segs) {
+    for (const LayerDesc &d : descs) {
         const long long n = (long long)d.tiles_m * d.tiles_n;
         const double c = (double)d.K + kTileFixedK;
         while (x < kXcds && cum + (double)n * c >= all * x / kXcds) {
@@ -81,7 +81,7 @@ tasq::XcdRuns cost_runs(const std::vector<LayerDesc> &segs, long long total)
 }
 
 // Cost of the busiest workgroup of a persistent launch over `runs`.
-double runs_makespan(const std::vector<LayerDesc> &segs, const tasq::XcdRuns &runs)
+double runs_makespan(const std::vector<LayerDesc> &descs, const tasq::XcdRuns &runs)
 {
     constexpr int wgs = tasq::kListWorkgroups / kXcds;
     double mx = 0;
@@ -89,9 +89,9 @@ double runs_makespan(const std::vector<LayerDesc> &segs, const tasq::XcdRuns &ru
     for (int x = 0; x < kXcds; ++x) {
         double load[wgs] = {0};
         for (int u = runs.begin[x], j = 0; u < runs.begin[x + 1]; ++u, j = (j + 1) % wgs) {
-            while (l + 1 < segs.size() && segs[l + 1].tile_begin <= u)
+            while (l + 1 < descs.size() && descs[l + 1].tile_begin <= u)
                 ++l;
-            load[j] += segs[l].K + kListFixedK;
+            load[j] += descs[l].K + kListFixedK;
         }
         mx = std::max(mx, *std::max_element(load, load + wgs));
     }
@@ -110,12 +110,12 @@ double runs_makespan(const std::vector<LayerDesc> &segs, const tasq::XcdRuns &ru
 // It is computed on every call, before the first launch, so costs are whole
 // numbers in flat arrays (20 us for the 804 tiles above; 120 with a growing list
 // per workgroup).
-double unit_lists(const std::vector<LayerDesc> &segs, std::vector<uint16_t> &order)
+double unit_lists(const std::vector<LayerDesc> &descs, std::vector<uint16_t> &order)
 {
     constexpr int W = tasq::kListWorkgroups, wgs = W / kXcds;
     std::vector<const LayerDesc *> by_k;
-    by_k.reserve(segs.size());
-    for (const LayerDesc &d : segs)
+    by_k.reserve(descs.size());
+    for (const LayerDesc &d : descs)
         by_k.push_back(&d);
     std::stable_sort(by_k.begin(), by_k.end(),
                      [](const LayerDesc *a, const LayerDesc *b) { return a->K > b->K; });
@@ -455,10 +455,14 @@ size_t max_split_bytes(const tasq_layer *layers, int L)
     return (size_t)mx;
 }
 
+// Room of a layer in the schedule's workspace, for its descriptor and a share
+// of the unit lists.
+constexpr size_t kLayerRoom = 1408;
+static_assert(sizeof(LayerDesc) <= kLayerRoom && sizeof(LayerDesc) % 4 == 0);
+
 constexpr size_t schedule_partials_offset(int L)
 {
-    return round_up((size_t)L * kXcds * sizeof(LayerDesc), kWsAlign) +
-           round_up((size_t)L * 64, kWsAlign);
+    return round_up((size_t)L * kLayerRoom, kWsAlign) + round_up((size_t)L * 64, kWsAlign);
 }
 
 // Estimated us of a layer cut into s ranges of K, fitted to 60 layers
@@ -1506,7 +1510,7 @@ static int run_schedule_impl(const tasq_layer *layers, int L, const uint8_t *b_t
             any_conv = any_conv || descs[l].kind == tasq::KIND_CONV3X3;
         tasq::TileShape ts = {32, 32, 128};
         hipError_t (*launch_step)(const LayerDesc *, int, int, const uint8_t *, int, int, bool,
-                                  hipStream_t) = nullptr;
+                                  bool, hipStream_t) = nullptr;
         hipError_t (*launch_persistent)(const LayerDesc *, int, int, const tasq::XcdRuns &,
                                         const uint8_t *, int, int, int, int,
                                         hipStream_t) = nullptr;
@@ -1561,7 +1565,6 @@ static int run_schedule_impl(const tasq_layer *layers, int L, const uint8_t *b_t
             LayerDesc &d = descs[l];
             d.tiles_m = (d.M + ts.bm - 1) / ts.bm;
             d.tiles_n = (d.N + ts.bn - 1) / ts.bn;
-            d.tile_first = 0;
             d.tile_begin = (int)total;
             total += (long long)d.tiles_m * d.tiles_n;
             if (total > 0x7fffffffLL)
@@ -1578,59 +1581,32 @@ static int run_schedule_impl(const tasq_layer *layers, int L, const uint8_t *b_t
         // cost (cost_runs), the one-workgroup-per-tile launches runs equal in
         // count.  For the latter, when the layers' tiles differ in cost (K)
         // and the layer order leaves one run much heavier than the others,
-        // every layer is cut into kXcds rounds instead, so that each run
-        // holds about an eighth of every layer (measured slower than
-        // contiguous runs for the persistent step: 4.27 against 4.15 ms).
-        std::vector<LayerDesc> segs;
-        if (!all_skinny && !launch_persistent &&
-            xcd_imbalance(descs, total) > kImbalanceLimit) {
-            segs.reserve((size_t)LG * kXcds);
-            // Unit p of the layer order counts towards run p % kXcds, so that
-            // the rounds have the very sizes of the XCDs' runs (xcd_remap)
-            // and no run ends with the next round's first tiles.
-            auto before = [](long long p, int r) { return (p + kXcds - 1 - r) / kXcds; };
-            std::vector<long long> next(LG, 0);
-            long long begin = 0;
-            for (int r = 0; r < kXcds; ++r)
-                for (int l = 0; l < LG; ++l) {
-                    const long long p = descs[l].tile_begin;
-                    const long long n = (long long)descs[l].tiles_m * descs[l].tiles_n;
-                    const long long lo = next[l], hi = lo + before(p + n, r) - before(p, r);
-                    if (hi <= lo)
-                        continue;
-                    next[l] = hi;
-                    LayerDesc d = descs[l];
-                    d.tile_first = (int)lo;
-                    d.tile_begin = (int)begin;
-                    begin += hi - lo;
-                    segs.push_back(d);
-                }
-        } else {
-            segs = descs;
-        }
-        const int nseg = (int)segs.size();
-        const tasq::XcdRuns runs = cost_runs(segs, total);
+        // every XCD takes an eighth of every layer instead (grouped_unit;
+        // measured slower than contiguous runs for the persistent step: 4.27
+        // against 4.15 ms).
+        const bool rounds = !all_skinny && !launch_persistent &&
+                            xcd_imbalance(descs, total) > kImbalanceLimit;
+        const tasq::XcdRuns runs = cost_runs(descs, total);
         // The persistent step over lists of units where they spare the
         // busiest workgroup enough of its work, and where they fit the part
-        // of the layer list's room that a persistent launch leaves unused
-        // (one descriptor of kXcds per layer).
-        const size_t desc_bytes = (size_t)nseg * sizeof(LayerDesc);
+        // of the layer list's room that the descriptors leave unused.
+        const size_t desc_bytes = (size_t)LG * sizeof(LayerDesc);
         const size_t order_at = round_up(desc_bytes + (size_t)L * S, 16);
         std::vector<uint16_t> order;
         if (!launch_persistent || total > kListMaxUnits ||
             (opts && (opts->persistent_wgs || opts->persistent_parties)))
             launch_lists = nullptr;
         if (launch_lists) {
-            if (unit_lists(segs, order) > kListGain * runs_makespan(segs, runs) ||
+            if (unit_lists(descs, order) > kListGain * runs_makespan(descs, runs) ||
                 order_at + 2 * order.size() > schedule_partials_offset(L)) {
                 order.clear();
                 launch_lists = nullptr;
             }
         }
-        // The segments, the table, then the lists, in one block of the
+        // The descriptors, the table, then the lists, in one block of the
         // workspace.
         std::vector<uint8_t> block(order_at + round_up(2 * order.size(), 16), 0);
-        std::memcpy(block.data(), segs.data(), desc_bytes);
+        std::memcpy(block.data(), descs.data(), desc_bytes);
         std::memcpy(block.data() + desc_bytes, b_table, (size_t)L * S);
         if (!order.empty())
             std::memcpy(block.data() + order_at, order.data(), 2 * order.size());
@@ -1662,13 +1638,14 @@ static int run_schedule_impl(const tasq_layer *layers, int L, const uint8_t *b_t
                 continue;
             }
             const hipError_t e =
-                all_skinny ? tasq::launch_skinny_grouped(d_descs, nseg, (int)total, max_m, src,
+                all_skinny ? tasq::launch_skinny_grouped(d_descs, LG, (int)total, max_m, src,
                                                          d_table, S, s, st)
-                : launch_lists ? launch_lists(d_descs, nseg, d_order, d_table, S, s, st)
+                : launch_lists ? launch_lists(d_descs, LG, d_order, d_table, S, s, st)
                 : launch_persistent
-                    ? launch_persistent(d_descs, nseg, (int)total, runs, d_table, S, s,
+                    ? launch_persistent(d_descs, LG, (int)total, runs, d_table, S, s,
                                         wgs_per_xcd, parties, st)
-                    : launch_step(d_descs, nseg, (int)total, d_table, S, s, any_conv, st);
+                    : launch_step(d_descs, LG, (int)total, d_table, S, s, any_conv,
+                                  rounds, st);
             if (e != hipSuccess)
                 return TASQ_ERR_HIP;
             if (int rc = record_step_event(opts, 2 * (t - t_begin) + 1, st))
@@ -1692,7 +1669,7 @@ static int run_schedule_impl(const tasq_layer *layers, int L, const uint8_t *b_t
     return TASQ_OK;
 }
 
-// The host-side lists (layer descriptors, segments, the table copy) are
+// The host-side lists (layer descriptors, unit lists, the table copy) are
 // std::vectors: running out of host memory is returned as TASQ_ERR_HIP, not
 // thrown across the C ABI.
 int tasq_run_schedule(const tasq_layer *layers, int L, const uint8_t *b_table, int S, int T,

@@ -35,9 +35,8 @@ struct LayerDesc {
     int32_t bits;           // effective precision b (single calls)
     int32_t lr_r;           // rank of the low-rank branch (16 or 32) when lr_T is set
     int32_t tiles_m, tiles_n;
-    int32_t tile_begin;     // first work unit of this segment in a grouped launch
-    int32_t tile_first;     // the segment's first tile within its layer
-    int32_t layer;          // row of the segment's layer in the (layer, stage) table
+    int32_t tile_begin;     // the layer's first work unit in a grouped launch
+    int32_t layer;          // the layer's row in the (layer, stage) table
 };
 
 // Per-byte keep mask for b effective bits, replicated over the 4 bytes of a
@@ -81,9 +80,10 @@ struct TileOps {
     hipError_t (*single)(const LayerDesc &d, bool aligned, hipStream_t stream);
     hipError_t (*planes)(const LayerDesc &d, bool aligned, hipStream_t stream);
     // One launch over every layer's tiles; any_conv selects the kernel that
-    // also handles 3x3 conv layers.
+    // also handles 3x3 conv layers, rounds the order of the units
+    // (grouped_unit).
     hipError_t (*grouped)(const LayerDesc *d_descs, int L, int total_tiles,
-                          const uint8_t *d_table, int S, int stage, bool any_conv,
+                          const uint8_t *d_table, int S, int stage, bool any_conv, bool rounds,
                           hipStream_t stream);
     // Split-K partials (aligned operands only) into part[splits][M][N].
     hipError_t (*split)(const LayerDesc &d, int32_t *part, int splits, int kchunk,
@@ -116,7 +116,7 @@ hipError_t launch_kgroups(const LayerDesc &d, KGroupTile tile, bool aligned, hip
 // linear layers only).
 hipError_t launch_kgroups_2x64(const LayerDesc *d_descs, int L, int total_tiles,
                                const uint8_t *d_table, int S, int stage, bool any_conv,
-                               hipStream_t stream);
+                               bool rounds, hipStream_t stream);
 
 // Sums split-K partials and applies the dequantisation epilogue (splitk.hip).
 hipError_t launch_split_finish(const LayerDesc &d, const int32_t *part, int splits,
@@ -139,7 +139,7 @@ struct PackedTileOps {
     TileShape shape;
     hipError_t (*single)(const LayerDesc &d, bool aligned, hipStream_t stream);
     hipError_t (*grouped)(const LayerDesc *d_descs, int L, int total_tiles,
-                          const uint8_t *d_table, int S, int stage, bool any_conv,
+                          const uint8_t *d_table, int S, int stage, bool any_conv, bool rounds,
                           hipStream_t stream);
     // Persistent grouped step (linear layers, no low-rank or weight-zero-
     // point terms), or null for tiles without one.
