@@ -35,14 +35,18 @@ constexpr double kImbalanceLimit = 1.10;
 constexpr double kTileFixedK = 384.0;
 
 // Persistent steps of up to this many tiles run over lists of units, which the
-// host deals out on each call, where these cut the busiest workgroup's cost by
-// a tenth.  us per step, runs / lists: 1 PixArt block at 4096 tokens (672
-// tiles) 107 / 83, 6 at 700 (756) 109.5 / 97.6, 1 SANA block at 3000 (1068)
+// host deals out on each call, where these cut the busiest workgroup's cost to
+// 0.87 of the runs'.  us per step, runs / lists: 1 PixArt block at 4096 tokens
+// (672 tiles) 107 / 83, 6 at 700 (756) 109.5 / 97.6, 1 SANA block at 3000 (1068)
 // 197.8 / 179.4, 2 PixArt blocks at 4096 (1344) 165.2 / 157.3; but 6 at 2048
 // (2016) 225.3 / 231.1: six tiles per workgroup and more even out, and layers
 // in turn keep the stores of shallow tiles under the matrix work of deep ones.
+// The line of 0.87: at 0.85 16 SANA blocks at 256 tokens 370 / 330 and 8 PixArt
+// blocks at 700 120.9 / 120.9, at 0.873 8 PixArt blocks at 1024 159.3 / 168.5 and 16 at
+// 500 184.8 / 188.4 (a run there is an XCD's own block or two, its tail of deep
+// tiles alone with the memory), at 0.886 4 blocks at 2048 164.4 / 161.1.
 constexpr long long kListMaxUnits = 1536;
-constexpr double kListGain = 0.9;
+constexpr double kListGain = 0.87;
 constexpr long long kStepCostMaxTiles = 4096;   // pick_step_tile
 // A tile of theirs takes about 8.5 us plus 1.6 per K tile of 128 bytes.
 constexpr double kListFixedK = 680.0;
