@@ -152,8 +152,8 @@ enum {
  *                   low-rank or weight-zero-point terms only on row-major
  *                   weights and the TASQ_TILE_256x256_K128_W8 tile): 1 = one
  *                   workgroup per output tile, 2 = the persistent launch
- *                   (one workgroup per compute unit walking a run of tiles),
- *                   whatever the tile and the tile count.
+ *                   (one workgroup per compute unit walking a run or a list
+ *                   of tiles), whatever the tile and the tile count.
  *   persistent_wgs  workgroups per XCD of the persistent launch (1..1024;
  *                   0 = one per compute unit, 32).
  *   persistent_parties  parts of each XCD's run of tiles walked side by side
@@ -492,8 +492,9 @@ typedef struct tasq_layer {
  * bytes, each step is one grouped launch over every layer's work; without it
  * each layer is launched separately.  The grouped launch streams the weights
  * (one workgroup per 32 output channels) when every layer has M <= 64 and
- * the same weight source (bit planes with the BITPLANE variant, packed
- * buffers, or row-major W); otherwise it tiles every layer's GEMM, reading
+ * one weight source serves them all (bit planes, packed buffers or row-major
+ * W; where AUTO would read different copies in different layers, the first of
+ * these that every layer has); otherwise it tiles every layer's GEMM, reading
  * the packed weights when every layer carries W_packed (W may then be NULL)
  * and the row-major W otherwise.  With row-major weights, a layer whose one
  * 256x256 output tile would cost more than a compute unit's even share of
@@ -510,8 +511,8 @@ int tasq_run_schedule(const tasq_layer *layers, int L, const uint8_t *b_table, i
                       int t_begin, int t_end, const tasq_opts *opts, void *stream);
 
 /* Limits of tasq_run_schedule_noalloc: layers per call, and the bytes of
- * the scratch array it keeps in each GPU's memory (the device layer list,
- * room for 8 segments of 176 bytes per layer, and the bit table). */
+ * the scratch array it keeps in each GPU's memory (the device layer list
+ * with lists of tiles, 1408 bytes per layer, and the bit table, 64). */
 #define TASQ_STATIC_MAX_LAYERS 256
 #define TASQ_STATIC_SCRATCH_BYTES 376832
 
@@ -538,8 +539,9 @@ int tasq_run_schedule_noalloc(const tasq_layer *layers, int L, const uint8_t *b_
                               void *stream);
 
 /* Workspace with which a single layer call (split_k = 0) cuts K into ranges:
- * splits * M * N * 4 bytes, or 0 when it would not split this shape (enough
- * output tiles, or K too short).  A smaller workspace runs unsplit. */
+ * M * N * 4 bytes for each of the most ranges that the library takes at this
+ * shape (a call may take fewer), or 0 when it would not split this shape
+ * (enough output tiles, or K too short).  A smaller workspace runs unsplit. */
 size_t tasq_workspace_bytes(int M, int N, int K);
 
 /* Workspace for the grouped schedule over these layers (host array): the

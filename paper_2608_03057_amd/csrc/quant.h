@@ -17,8 +17,10 @@ namespace tasq {
 // (with its row kept in registers); large tensors stay bound by memory.
 //
 // Out of range, exact is false and the caller divides.  Where x itself is so
-// small that the residual loses bits, the quotient is below 2^-60 and its
-// last bit decides no code.
+// small (about 2^-103) that the residual loses bits, the quotient is below
+// 2^-42 and may be off in its last bits, which decide no code: beside a z of
+// 2^-18 and more it vanishes in the sum, and with a smaller z the sum, next to
+// zero, rounds to 0 and floors to 0 or -1, all of them code 0.
 struct Divider {
     float d, r;
     bool exact;

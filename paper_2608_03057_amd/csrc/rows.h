@@ -40,8 +40,9 @@ __device__ __forceinline__ v4i ld16(rsrc_t r, uint32_t off)
 // Bound by instruction issue and latency like the aligned path: the extra
 // dword load and shifts hide behind the matrix work of the other waves.
 // A call in a row of calls, against byte-by-byte loads (sixteen per chunk):
-// 777x1153 -> 1111 12.6 us (62.5 before, both with 64x64 tiles), 8192x1151 ->
-// 3456 64.2 us (361.7), a 20x30 conv 1275 -> 1280 64.9 us (1217).
+// 777x1153 -> 1111 12.6 us (62.5 before, both with 64x64 tiles; 8.3 with K
+// shared by wave groups as well), 8192x1151 -> 3456 64.2 us (361.7), a 20x30 conv
+// 1275 -> 1280 64.9 us (1217).
 //
 // window_fits: rows * K bytes, the partial dwords at both ends and every
 // offset into them stay below kOOB.

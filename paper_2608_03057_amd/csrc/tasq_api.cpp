@@ -630,12 +630,16 @@ enum WeightSrc { SRC_NONE = 0, SRC_ROWS, SRC_PACKED, SRC_PLANES };
 // the int8 copies, and the bit-plane GEMM only when no other copy is given.
 // Between the two int8 copies (both given):
 //   * a single layer takes the packed copy when it has more than one
-//     256x256 tile per two compute units, the rows otherwise.  Measured per
-//     layer (us, b = 8, cold cache, rows / packed): PixArt QKV 8192x1152x3456
-//     (448 tiles) 60.4 / 57.0, MLP-up (576) 82.6 / 78.0, MLP-down (160)
-//     72.5 / 71.0, SANA GLU-up (704) 145.4 / 133.4; SDXL-Turbo A-QKV (128)
-//     17.8 / 18.4, B-QKV (60) 17.9 / 21.6, B-ff-down (20) 30.6 / 33.9, the
-//     3x3 conv (20) 69.4 / 71.5, 256x1152x1152 (5) 10.6 / 12.1;
+//     256x256 tile per two compute units, the rows otherwise.  us of a call
+//     in a row of calls (b = 5), rows / packed: 1024x1280 -> 3840 (60 tiles)
+//     10.0 / 11.0, 1500x1152 -> 4608 (108) 13.0 / 13.9, 4096x640 -> 1920 (128)
+//     11.1 / 11.6, 4096x2240 -> 2240 (144) 29.7 / 29.7, 8192x1152 -> 1152 (160)
+//     20.2 / 18.3, 8192x1152 -> 3456 (448) 46.2 / 43.5, 8192x1152 -> 4608 (576)
+//     66.6 / 54.9, 4096x2240 -> 11200 (704) 112.8 / 113.7, 16384x1152 -> 4608
+//     (1152) 110.7 / 104.3.  The line leaves out some deep layers below it
+//     (3000x5600 -> 2240, 108 tiles, 53.6 / 44.6) and the largest ones, where
+//     the rows' walk is ahead by 1 to 5% (16384x2240 -> 6720, 1728 tiles, 257 /
+//     269);
 //   * on byte-aligned activations (a K that is no multiple of 16, an odd
 //     address) a linear layer takes the packed copy, whose weights need no
 //     shifts (rows / packed: 4942x861 -> 640 15.6 / 12.4, 4096x2241 -> 2240
