@@ -1,8 +1,8 @@
 """Single layers whose K range is shared by groups of waves, and the single
 persistent walk, through the library's own choice, at the sizes where its
-rules change and where groups run out of K tiles: int32 bit-exact and fp32
-within 1e-6 of the dequantised magnitude against the oracle, every epilogue
-term at once on some."""
+rules change and where groups run out of K tiles, and the walk forced on short
+K: int32 bit-exact and fp32 within 1e-6 of the dequantised magnitude against
+the oracle, with a bias, and a low-rank branch on some."""
 import numpy as np
 import pytest
 import torch
@@ -51,10 +51,12 @@ def test_groups_conv(H, Wd, C, N):
                   np.asarray(ry).reshape(-1, N), SX, sw, bias, f"conv {(H, Wd, C, N)}")
 
 
-# Tile counts around one and two rounds of the compute units, one K tile and
-# several, ragged in every size; the tail XCDs' runs differ in length.
+# Ragged in every size, by the estimates of 256x256 tiles walked and of 128x128
+# tiles: 128x128 (20.2 us against 20.6, 29.6 / 41.3, 37.4 / 44.0), nearly level
+# (94.4 / 95.1), and the walk with one tile per workgroup (31.5 / 47.1) and with
+# three (61.9 / 80.5), the XCDs' runs of unequal length.
 @pytest.mark.parametrize("M,N,K", [(2300, 4000, 1152), (4100, 4090, 1040), (8200, 2305, 1168),
-                                   (12000, 2816, 2064)])
+                                   (12000, 2816, 2064), (4000, 4000, 2064), (4200, 11100, 1040)])
 @pytest.mark.parametrize("extras", [False, True])
 def test_single_walk(M, N, K, extras):
     X, W, sw, bias = rows_cols(M, N, K, 8400 + M)
@@ -86,3 +88,22 @@ def test_single_walk(M, N, K, extras):
         ref = ref + (t @ u.T).numpy()
         tol = tol + (2.0 ** -16 + 70 * 2.0 ** -24) * (t.abs() @ u.abs().T).numpy()
     assert np.all(np.abs(y.cpu().numpy().astype(np.float64)[rr, cc] - ref) <= tol)
+
+
+# The walk over two tiles per workgroup (17 x 17 of 256x256) where the stages
+# and register slots turn over within a tile: one K tile, short and whole, two
+# and three, with and without a remainder.  Every entry, on the GPU in float64.
+@pytest.mark.parametrize("K", [16, 128, 144, 256, 272, 400])
+@pytest.mark.parametrize("M,N", [(4130, 4100), (8200, 2305)])
+def test_forced_walk(M, N, K):
+    X, W, sw, bias = (t.to(DEV) for t in rows_cols(M, N, K, 8500 + K))
+    for b in (8, 3):
+        acc, y = T.masked_linear(X, W, SX, sw, b, bias, tune=dict(tile=1))
+        torch.cuda.synchronize()
+        step = 2 ** (8 - b)
+        Wb = (torch.div(W.int(), step, rounding_mode="floor") * step).double()
+        ra = X.double() @ Wb.T.contiguous()
+        assert torch.equal(acc, ra.to(torch.int32)), f"K={K} b={b}"
+        main = ra * (SX * sw.double())
+        tol = 1e-6 * (main.abs() + bias.double().abs())
+        assert bool(((y.double() - (main + bias.double())).abs() <= tol).all()), f"K={K} b={b}"

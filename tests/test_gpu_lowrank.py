@@ -7,9 +7,10 @@ Bar.  Codes, alpha, z and int32 accumulators: bit-exact.  The branch is
 compared against its fp64 value lr64 with the bound derived from the
 kernels' arithmetic, relative to S[m,n] = sum_j |U[n,j]| A[m,j],
 A[m,j] = sum_k |bf16(x[m,k]) D[j,k]|:
-  * T: fp32 MFMA accumulation, at most ceil(K/16) MFMAs per wave of 16
-    products each, then a fixed-order sum of 8 wave partials:
-    (ceil(K/16) + 24) u A[m,j], u = 2^-24;
+  * T: fp32 MFMA accumulation, 16 waves with ceil(K/512) MFMAs of 32
+    products at most each, then a fixed-order sum of the wave partials:
+    within (ceil(K/16) + 24) u A[m,j], u = 2^-24, twice the K steps and the
+    16 partials;
   * T as two bfloat16 parts (exact truncation, then the remainder rounded):
     2^-16 |T|;
   * T U^T: 2 ceil(r/16) bfloat16 MFMAs of 16 products (weight-streaming
