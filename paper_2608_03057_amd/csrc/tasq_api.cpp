@@ -354,6 +354,16 @@ double cost_128(long long tiles, long long nk, bool rank32)
 // second round a quarter full) 23.7 / 30.9, 2048x1280 -> 10240 (320) 34.2 /
 // 42.4, 8192x1152 -> 3456 (448) 48.9 / 46.9, 4096x2240 -> 2240 (144) 40.0 /
 // 33.8, 4096x2240 -> 11200 (704) 124.6 / 104.6.
+// From 140 to 256 tiles of 256x256 with K above 1024 always the walk: the
+// estimates come from operands that stay in the caches, where the two are
+// within 7%, and 128x128 tiles read each operand twice as often, which shows
+// on operands that are new to the chip.  us, 128x128 / 256x256, the same
+// buffers each call and then new ones: 1024x1280 -> 10240 (160 tiles) 22.1 /
+// 22.7 and 28.7 / 23.8, 8192x1152 -> 1152 (160) 21.2 / 20.7 and 22.8 / 21.1,
+// 2048x1152 -> 4608 (144) 20.3 / 21.0 and 22.1 / 20.8, 4096x1152 -> 3456 (224)
+// 25.3 / 25.1 and 31.1 / 26.2.  With a short K 128x128 is as good or better on
+// both: 3000x320 -> 4096 (192) 14.7 / 16.0 and 14.9 / 16.3, 3000x640 -> 5120
+// (240) 19.2 / 20.7 and 19.9 / 21.6.
 // Byte-aligned operands have no persistent walk: 256x256 tiles from 140 up
 // (8192x1151 -> 3456 64 us against 69), and none for a conv, whose chunks'
 // taps and shifts need more registers than that tile leaves (96x96 pixels
@@ -367,8 +377,9 @@ int pick_tile(const tasq_opts *o, long long M, long long N, long long K, bool al
     const long long t256 = ((M + 255) / 256) * ((N + 255) / 256);
     const long long t128 = ((M + 127) / 128) * ((N + 127) / 128);
     const long long nk = (K + 127) / 128;
-    const bool big = aligned && !conv ? cost_256(t256, nk, rank32) <
-                                            cost_128(t128, nk, rank32)
+    const bool one_round = t256 >= 140 && t256 <= kComputeUnits && K > 1024;
+    const bool big = aligned && !conv ? one_round || cost_256(t256, nk, rank32) <
+                                                         cost_128(t128, nk, rank32)
                                       : t256 >= 140 && (aligned || !conv);
     if (t128 >= 200 && big)
         return tasq::TILE_256x256_K128_W8_PF1;
