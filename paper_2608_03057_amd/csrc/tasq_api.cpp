@@ -281,16 +281,22 @@ int persistent_parties(const tasq_opts *o, int wgs_per_xcd)
     return wgs_per_xcd % p == 0 ? p : 1;
 }
 
-// Packed-weight tile of a single launch, from a sweep of every tile over the
-// DiT/UNet layer shapes with the Infinity Cache flushed before each launch:
-// the 256x256 tile for 140 tiles up to one per compute unit (even half a
-// round of 256x256 tiles beats 2-3 of smaller ones from about there) and for
-// the largest layers, the 4-wave 128x256 tile (two workgroups per CU, one's
-// stores under the other's matrix work) while it gives 200 tiles, and 64x64
-// tiles below that.  us, 128x256 / 256x256: 4096x2240 -> 2240 (144 tiles of
-// 256x256) 36.1 / 33.7, 8192x1152 -> 3456 (448) 42.1 / 49.7, 8192x1152 -> 4608
-// (576) 51.1 / 66.3, 4096x2240 -> 11200 (704) 109.3 / 115.4, 6278x11200 -> 3456
-// (350) 229 / 259, 8192x8192 -> 8192 462 / 435.
+// Packed-weight tile of a single launch, from sweeps of every tile over the
+// DiT/UNet layer shapes: the 256x256 tile for 140 tiles up to one per compute
+// unit (even half a round of 256x256 tiles beats 2-3 of smaller ones from about
+// there) and for the largest layers, the 4-wave 128x256 tile (two workgroups
+// per CU, one's stores under the other's matrix work) while it gives 200 tiles,
+// and 64x64 tiles below that.  us, 128x256 / 256x256, the same buffers each call
+// and then new ones: 8192x1152 -> 3456 (448 tiles of 256x256) 43.0 / 47.7 and
+// 45.1 / 48.0, 8192x1152 -> 4608 (576) 55.3 / 67.1 and 56.1 / 67.4, 3000x2240 ->
+// 6720 (324) 57.2 / 67.3 and 59.6 / 67.7, 16384x5600 -> 2240 (576) 206 / 223 and
+// 231 / 234, 4096x2240 -> 11200 (704) 111 / 115 and 116 / 116; on the same
+// buffers 4096x2240 -> 2240 (144) 36.1 / 33.7, 8192x8192 -> 8192 462 / 435.  Over
+// 39 layers of 257 to 1056 tiles it takes 0.87 and 0.91 of the 256x256 tile's
+// time, and more by over 2% on two with new buffers (2048x2240 -> 11200 76.1 /
+// 74.6, 4096x2240 -> 6720 84.6 / 75.4).  Right after a 512 MB fill, which leaves
+// the caches full of written lines, it is slower by up to 18% (8192x1152 -> 3456
+// 62 / 55, 4096x2240 -> 6720 101 / 86).
 // A conv's taps need more registers than the 128x256 tile leaves (its conv
 // kernel spills): 256x256 from 140 tiles up whatever their number (us, 128x256 /
 // 256x256: 96x96 pixels 1280 -> 2560 434 / 303, 160x160 640 -> 640 187 / 153,
