@@ -282,21 +282,29 @@ int persistent_parties(const tasq_opts *o, int wgs_per_xcd)
 }
 
 // Packed-weight tile of a single launch, from sweeps of every tile over the
-// DiT/UNet layer shapes: the 256x256 tile for 140 tiles up to one per compute
-// unit (even half a round of 256x256 tiles beats 2-3 of smaller ones from about
-// there) and for the largest layers, the 4-wave 128x256 tile (two workgroups
-// per CU, one's stores under the other's matrix work) while it gives 200 tiles,
-// and 64x64 tiles below that.  us, 128x256 / 256x256, the same buffers each call
-// and then new ones: 8192x1152 -> 3456 (448 tiles of 256x256) 43.0 / 47.7 and
-// 45.1 / 48.0, 8192x1152 -> 4608 (576) 55.3 / 67.1 and 56.1 / 67.4, 3000x2240 ->
-// 6720 (324) 57.2 / 67.3 and 59.6 / 67.7, 16384x5600 -> 2240 (576) 206 / 223 and
-// 231 / 234, 4096x2240 -> 11200 (704) 111 / 115 and 116 / 116; on the same
-// buffers 4096x2240 -> 2240 (144) 36.1 / 33.7, 8192x8192 -> 8192 462 / 435.  Over
-// 39 layers of 257 to 1056 tiles it takes 0.87 and 0.91 of the 256x256 tile's
-// time, and more by over 2% on two with new buffers (2048x2240 -> 11200 76.1 /
-// 74.6, 4096x2240 -> 6720 84.6 / 75.4).  Right after a 512 MB fill, which leaves
-// the caches full of written lines, it is slower by up to 18% (8192x1152 -> 3456
-// 62 / 55, 4096x2240 -> 6720 101 / 86).
+// DiT/UNet layer shapes and a grid of K 1152..8192 at 288 to 1280 tiles: 64x64
+// tiles below 200 of 128x256, the 4-wave 128x256 tile (two workgroups per CU,
+// one's stores under the other's matrix work) from there, and 256x256
+//   * from 140 of them up to one per compute unit: even half a round of them
+//     beats 2-3 of smaller ones from about there;
+//   * above that where K is over 2048 and the last round has 140 tiles or
+//     more: a 128x256 tile reads each weight twice as often, which K pays for,
+//     most on buffers that are new to the chip, while the stores it hides
+//     don't grow with K;
+//   * for the largest layers.
+// us, 128x256 / 256x256, the same buffers each call and then new ones: 8192x1152
+// -> 3456 (448 tiles of 256x256) 43.0 / 47.7 and 45.1 / 48.0, 8192x1152 -> 4608
+// (576) 55.3 / 67.1 and 56.1 / 67.4, 6000x2240 -> 6720 (648) 101 / 109 and 100 /
+// 108, 16384x5600 -> 2240 (576) 206 / 223 and 231 / 234; 4096x2240 -> 6720 (432)
+// 73.8 / 74.9 and 84.6 / 75.4, 4096x3072 -> 6720 (432) 88.7 / 89.6 and 105 / 92.4,
+// 4096x4608 -> 6720 128 / 124 and 151 / 130; on the same buffers 4096x2240 -> 2240
+// (144) 36.1 / 33.7, 8192x8192 -> 8192 462 / 435.  Above a round, 128x256 over
+// 256x256 on the grid: K up to 2048 0.79 to 0.98, and 0.81 to 1.01 on new
+// buffers (2048x2048 -> 16128 1.13, 1200x1152 -> 24000 1.08); deeper with a shorter last round 0.84 to
+// 0.98 and 0.92 to 1.04; deeper with 140 tiles or more in it 0.95 to 1.10 and
+// 1.00 to 1.23.  Right after a 512 MB fill, which leaves the caches full of
+// written lines, 128x256 tiles are slower by up to 12% (8192x1152 -> 3456 62 /
+// 55).
 // A conv's taps need more registers than the 128x256 tile leaves (its conv
 // kernel spills): 256x256 from 140 tiles up whatever their number (us, 128x256 /
 // 256x256: 96x96 pixels 1280 -> 2560 434 / 303, 160x160 640 -> 640 187 / 153,
@@ -308,7 +316,9 @@ int pick_packed_tile(const tasq_opts *o, long long M, long long N, long long K, 
         return f;
     const long long t256 = ((M + 255) / 256) * ((N + 255) / 256);
     const long long t128x256 = ((M + 127) / 128) * ((N + 255) / 256);
-    if ((t256 >= 140 && (conv || t256 <= kComputeUnits)) || M * N * K >= (1LL << 38))
+    const long long last = t256 % kComputeUnits;
+    const bool deep = K > 2048 && (last == 0 || last >= 140);
+    if ((t256 >= 140 && (conv || t256 <= kComputeUnits || deep)) || M * N * K >= (1LL << 38))
         return tasq::PTILE_256x256_K128_W8;
     if (t128x256 >= 200)
         return tasq::PTILE_128x256_K128_W4;

@@ -51,10 +51,11 @@ def test_groups_conv(H, Wd, C, N):
                   np.asarray(ry).reshape(-1, N), SX, sw, bias, f"conv {(H, Wd, C, N)}")
 
 
-# Ragged in every size, by the estimates of 256x256 tiles walked and of 128x128
-# tiles: 128x128 (20.2 us against 20.6, 29.6 / 41.3, 37.4 / 44.0), nearly level
-# (94.4 / 95.1), and the walk with one tile per workgroup (31.5 / 47.1) and with
-# three (61.9 / 80.5), the XCDs' runs of unequal length.
+# Ragged in every size: the walk at the fewest tiles that take it (144, level
+# with 128x128 by the estimates, 20.6 us against 20.2), 128x128 (29.6 us against
+# the walk's 41.3, 37.4 / 44.0), nearly level (94.4 / 95.1), and the walk with
+# one tile per workgroup (31.5 / 47.1) and with three (61.9 / 80.5), the XCDs'
+# runs of unequal length.
 @pytest.mark.parametrize("M,N,K", [(2300, 4000, 1152), (4100, 4090, 1040), (8200, 2305, 1168),
                                    (12000, 2816, 2064), (4000, 4000, 2064), (4200, 11100, 1040)])
 @pytest.mark.parametrize("extras", [False, True])

@@ -67,3 +67,19 @@ def test_packed_conv_of_many_tiles(H, Wd, C, N):
     torch.cuda.synchronize()
     assert torch.equal(acc, want)
     assert torch.allclose(y, wy, rtol=1e-6, atol=0.0)
+
+
+# Packed layers of more than one 256x256 tile per compute unit, on each side of
+# the lines between 256x256 and 128x256 tiles: a deep K with 144 tiles and with
+# none in the last round, with 104, and K 2048 with 144.
+@pytest.mark.parametrize("M,N,K", [(4990, 5000, 2064), (4000, 8190, 2192), (4990, 4600, 2064),
+                                   (4990, 5000, 2048)])
+def test_packed_linear_of_many_tiles(M, N, K):
+    X, W = operands(M + K, (M, K), (N, K))
+    sw = torch.rand(N, device=DEV) * 0.01
+    acc, y = T.masked_linear(X, None, SX, sw, 6, packed=T.pack_weights(W))
+    torch.cuda.synchronize()
+    ra = X.double() @ masked(W, 6).double().T.contiguous()
+    assert torch.equal(acc, ra.to(torch.int32))
+    ref = ra * (SX * sw.double())
+    assert bool(((y.double() - ref).abs() <= 1e-6 * ref.abs()).all())
